@@ -88,7 +88,9 @@ typedef struct {
                        - other 2-D grids of radius <= 3 on the matrix engines with a
                          16-bit carry: two;
                        - 1-D lines of radius <= 3 (16-bit or fp32 carry): up to four;
-                         automatic: four from 2^22 points, else two;
+                         automatic (and tile_h 0): four from 2^22 points, else two, and
+                         the launches advance up to 64 steps each in LDS, with the bits
+                         of launches of that many steps;
                        - 3-D grids: two for radius 1 with a 16-bit carry, only when asked
                          for (measured slower on the 512^3 and 256^3 workloads);
                        - the direct engine on 2-D grids of radius <= 3: up to 16 steps

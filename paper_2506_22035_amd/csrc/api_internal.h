@@ -22,6 +22,8 @@ struct spider_plan_s {
   int row_swap = 0;          // 1: explicit row swap through an LDS copy (ablation)
   int max_time_block = 1;    // deepest fusion this plan supports (paired 16-bit: 4)
   int direct_tile = 32;      // direct engine, several steps per launch: output tile side (16 or 32)
+  bool line_deep = false;    // 1-D line whose loops run in LDS, many steps per launch
+  int ncu = 256;             // compute units of the plan's device
   bool tune_depth = false;   // the autotuner also chooses time_block (2..max_time_block)
   int tile_h = 0;
   int use_graph = 1;
@@ -48,7 +50,7 @@ struct spider_plan_s {
   hipStream_t cap_stream = nullptr;
   std::map<std::tuple<const void*, const void*, int>, hipGraphExec_t> graphs;
   // long time loops: one graph of kGraphBody launches of one kind (steps per launch)
-  // between two buffers, replayed; keyed by (steps per launch, first source, first destination)
+  // between two buffers, replayed; keyed by (launch kind, or 16 + steps of a line's launch, first source, first destination)
   std::map<std::tuple<int, const void*, const void*>, hipGraphExec_t> body_graphs;
   std::mutex mu;
 };

@@ -112,6 +112,28 @@ hipError_t launch_band1d(int r, int operand, int engine, const BandGrid& g, hipS
 // wave, each wave also computing T - 1 blocks on either side for its neighbours.
 hipError_t launch_band1d_tbt(int r, int operand, int engine, int T, const BandGrid& g, hipStream_t s);
 
+// 1-D lines advanced up to kLineDeepMaxSteps steps per launch in LDS (r <= 3): one
+// wave per section of nb (4 or 8) blocks of 256 points.  io16: the grid is 16-bit; xlo: the
+// levels are kept as hi / lo pairs.  Bit s - 1 of `rounds` (io16 and xlo): step s
+// rounds the grid to 16 bits.  Operands as for launch_band1d.
+constexpr int kLineDeepMaxSteps = 64;
+struct LineDeep {
+  const void* in;
+  void* out;
+  const uint4* apack;
+  const uint32_t* ipack;
+  const uint4* dpack;
+  uint64_t rounds;
+  int nx, T, halo;
+  bool aligned;  // both grids start on a 16-byte boundary
+};
+struct LineChoice {
+  int nb = 0, sections = 0;
+};
+LineChoice line_deep_choice(int nx, int r, int T, int ncu);
+hipError_t launch_line_deep(int operand, int engine, bool io16, bool xlo, int r, int T, uint64_t rounds,
+                            const LineChoice& c, const BandGrid& g, hipStream_t s);
+
 // Resident 64-lane workgroups per CU of the 2-D band kernel (0 on error).
 int band2d_blocks_per_cu(int r, int operand, int engine, bool aligned);
 int band3d_blocks_per_cu(int r, int operand, int engine, bool aligned, uint32_t rowmask);

@@ -18,25 +18,12 @@
 #include <hip/hip_runtime.h>
 
 #include "band_common.h"
+#include "band_f32_common.h"
 #include "kernels.h"
 
 namespace spider_impl {
 
 namespace {
-
-// Split two consecutive fp32 values into packed 16-bit words hi = rnd(x) and
-// lo = rnd(x - hi) (x - hi is exact in fp32).
-template <int OP, bool XLO>
-__device__ __forceinline__ void split2(uint32_t a, uint32_t b, uint32_t* hi, uint32_t* lo) {
-  const float fa = __builtin_bit_cast(float, a), fb = __builtin_bit_cast(float, b);
-  *hi = pack2<OP>(fa, fb);
-  if constexpr (XLO) {
-    const f32x2 h = unpack2<OP>(*hi);
-    *lo = pack2<OP>(fa - h.x, fb - h.y);
-  } else {
-    *lo = 0u;
-  }
-}
 
 // A staged fp32 line covers x in [x0 - 8, x0 + 264) (x0 = strip origin of the
 // 16-bit kernel minus 8): lane l holds the 4 values at x0 - 8 + 4l and lanes
@@ -82,20 +69,6 @@ __device__ __forceinline__ F32Line load_h16_line(__amdgpu_buffer_rsrc_t rs, uint
   L.m = __builtin_bit_cast(u32x4, (f32x4){a.x, a.y, b.x, b.y});
   L.t = __builtin_bit_cast(uint32_t, t.x);
   return L;
-}
-
-// Store 4 fp32 outputs; the line resource drops whatever lies outside [0, nx).
-template <bool ALIGNED>
-__device__ __forceinline__ void store_f32x4(__amdgpu_buffer_rsrc_t rs, uint32_t voff, f32x4 v) {
-  if constexpr (ALIGNED) {
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, voff, 0, kStoreNT);
-  } else {
-    // Cast the whole vector: element-wise bit casts of a float vector feeding these
-    // stores have been seen to compile to four stores of element 0.
-    const u32x4 u = __builtin_bit_cast(u32x4, v);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) __builtin_amdgcn_raw_buffer_store_b32(u[t], rs, voff + 4 * t, 0, 0);
-  }
 }
 
 }  // namespace

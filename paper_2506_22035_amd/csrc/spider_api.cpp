@@ -383,11 +383,14 @@ static spider_status launch_rem2(spider_plan_s* p, const void* src, void* dst, h
 // written (unless in == out).  The direct engine's fused kernel takes any step
 // count, so its remainder is one launch of `rem` steps (in the place of the
 // two-step launches).
+// Lines advanced in LDS run launches of `deep` steps (a multiple of time_block)
+// and one of the remainder.
 struct LoopShape {
-  int fused;    // launches of time_block steps: k = 1 .. fused
-  int two;      // then two-step launches (direct engine: one launch of rem steps)
+  int fused;    // launches of time_block (or deep) steps: k = 1 .. fused
+  int two;      // then two-step launches (direct engine, deep: one launch of rem steps)
   int total;    // then single steps up to k = total
-  int rem = 0;  // direct engine: steps of the remainder launch
+  int rem = 0;  // direct engine, deep: steps of the remainder launch
+  int deep = 0;
   int kind(int k) const { return k <= fused ? 3 : (k <= fused + two ? 2 : 1); }
   int run_end(int k) const { return k <= fused ? fused : (k <= fused + two ? fused + two : total); }
 };
@@ -395,6 +398,20 @@ struct LoopShape {
 static LoopShape loop_launches(const spider_plan_s* p, int steps) {
   LoopShape L;
   const int tb = p->time_block;
+  if (p->line_deep) {
+    // the fewest launches, of equal depth: a launch's load, store and tail cost about
+    // as much as five steps of a long line; a section of 1024 points loses 2 T r of
+    // them to its halo (T = 64 at r = 1: 13 %, T = 48 at r = 3: 28 %)
+    const int max_t = p->r == 1 ? kLineDeepMaxSteps : 48;
+    const int n = std::max(1, (steps + max_t - 1) / max_t);
+    const int per = (steps + n - 1) / n;
+    L.deep = std::max(tb, std::min(max_t / tb * tb, (per + tb - 1) / tb * tb));
+    L.fused = steps / L.deep;
+    L.rem = steps - L.deep * L.fused;
+    L.two = L.rem > 0 ? 1 : 0;
+    L.total = L.fused + L.two;
+    return L;
+  }
   if (p->engine == SPIDER_ENGINE_DIRECT && tb >= 2) {
     L.fused = steps / tb;
     L.rem = steps - tb * L.fused;
@@ -409,6 +426,24 @@ static LoopShape loop_launches(const spider_plan_s* p, int steps) {
   return L;
 }
 
+// `steps` steps of a line in one launch in LDS.  A 16-bit grid with split 3 is
+// rounded where launches of time_block steps, then two-step launches and a single
+// step, would store it.
+static spider_status launch_line_steps(spider_plan_s* p, const void* src, void* dst, int steps, hipStream_t s) {
+  const int tb = p->time_block, main = tb * (steps / tb);
+  uint64_t rounds = 0;
+  for (int k = 1; k <= steps; ++k)
+    if (k <= main ? k % tb == 0 : (tb == 2 || (k - main) % 2 == 0 || k == steps)) rounds |= 1ull << (k - 1);
+  BandGrid g = p->grid_template;
+  g.in = src;
+  g.out = dst;
+  const LineChoice c = line_deep_choice(p->nx, p->r, steps, p->ncu);
+  const hipError_t e = launch_line_deep(p->operand, p->engine, p->carry != SPIDER_F32, p->split == 3, p->r, steps,
+                                        rounds, c, g, s);
+  if (e != hipSuccess) return hip_fail(e, "kernel launch");
+  return SPIDER_OK;
+}
+
 // Launches k in [k0, k1] of the loop `L`, reading `src` first.  Buffers b_k = out if
 // (L.total - k) is even, else `scratch` (the plan's own, or a server request's).
 static spider_status enqueue_launches(spider_plan_s* p, const void* src, void* out, void* scratch, int k0, int k1,
@@ -417,7 +452,8 @@ static spider_status enqueue_launches(spider_plan_s* p, const void* src, void* o
     void* dst = ((L.total - k) % 2 == 0) ? out : scratch;
     if (dst == src) return fail(SPIDER_ERR_INVALID, "internal: launch %d reads and writes one buffer", k);
     const int kind = L.kind(k);
-    spider_status st = kind == 3   ? launch_step2(p, src, dst, s)
+    spider_status st = L.deep      ? launch_line_steps(p, src, dst, kind == 3 ? L.deep : L.rem, s)
+                       : kind == 3 ? launch_step2(p, src, dst, s)
                        : kind == 2 ? (p->engine == SPIDER_ENGINE_DIRECT ? launch_direct_steps(p, src, dst, L.rem, s)
                                                                         : launch_rem2(p, src, dst, s))
                                    : launch_step(p, src, dst, s);
@@ -502,7 +538,7 @@ static spider_status enqueue_long(spider_plan_s* p, const void* in, void* out, c
     while (st == SPIDER_OK && run_end - k + 1 >= kGraphBody) {
       const void* from = ((total - (k - 1)) % 2 == 0) ? out : p->d_scratch;
       void* to = ((total - k) % 2 == 0) ? out : p->d_scratch;
-      auto key = std::make_tuple(kind, from, (const void*)to);
+      auto key = std::make_tuple(L.deep ? 16 + L.deep : kind, from, (const void*)to);
       auto it = p->body_graphs.find(key);
       if (it == p->body_graphs.end()) {
         hipGraphExec_t exec = nullptr;
@@ -638,6 +674,10 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     delete p;
     return hip_fail(e, "hipGetDevice");
   }
+  {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, p->device) == hipSuccess && n > 0) p->ncu = n;
+  }
 
   if (engine == SPIDER_ENGINE_DIRECT) {
     std::vector<char> buf(ncoef * dtype_bytes(p->carry));
@@ -768,13 +808,14 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
       T = ndim == 3   ? 1
           : ndim == 1 ? (pts >= (1LL << 22) ? 4 : 2)
                       : (pts >= (1LL << 25) ? 4 : pts >= (1LL << 23) ? 3 : 2);
-      p->tune_depth = o.autotune && o.tile_h == 0 && p->max_time_block > 2;
+      p->line_deep = tb1_ok && o.tile_h == 0;
+      p->tune_depth = o.autotune && o.tile_h == 0 && p->max_time_block > 2 && !p->line_deep;
     } else {
       T = o.time_block;
     }
     set_time_block(p, std::min(T, p->max_time_block), o.tile_h);
   }
-  if (o.autotune && o.tile_h == 0) {
+  if (o.autotune && o.tile_h == 0 && !p->line_deep) {
     spider_status st = ensure_scratch(p);
     if (st == SPIDER_OK) st = autotune_tile(p);
     if (st != SPIDER_OK) {
@@ -801,8 +842,9 @@ spider_status spider_apply(spider_plan_t p, const void* in, void* out, int steps
     if (st != SPIDER_OK) return st;
   }
   const LoopShape L = loop_launches(p, steps);
-  // a loop of one launch gains nothing from a graph but the graph's own launch cost
-  if (!p->use_graph || steps < 2 || L.total < 2) return enqueue_steps(p, in, out, steps, s);
+  // a loop of one launch gains nothing from a graph but the graph's own launch cost,
+  // nor does a line's loop of a few launches, each long enough to cover the next's
+  if (!p->use_graph || steps < 2 || L.total < 2 || (L.deep && L.total <= 8)) return enqueue_steps(p, in, out, steps, s);
   if (L.total > 2 * kGraphBody) return enqueue_long(p, in, out, L, s);
   // Replay a graph of the whole time loop, captured once per (in, out, steps).
   auto key = std::make_tuple(in, (const void*)out, steps);
@@ -936,7 +978,11 @@ spider_status spider_plan_work(spider_plan_t p, int steps, uint64_t* launches, u
   uint64_t n = 0;
   for (int k = 1; k <= total; ++k) {
     const int kind = L.kind(k);
-    if (line)
+    if (L.deep) {
+      const int T = kind == 3 ? L.deep : L.rem, f = p->split == 3 ? 2 : 1;
+      const LineChoice c = line_deep_choice(p->nx, p->r, T, p->ncu);
+      n += (uint64_t)c.sections * c.nb * T * f * (p->engine == SPIDER_ENGINE_DENSE ? 2 : 1);
+    } else if (line)
       n += kind == 3   ? line_launch_instructions(p, p->grid_tb2, p->time_block)
            : kind == 2 ? line_launch_instructions(p, p->grid_rem2, 2)
                        : line_launch_instructions(p, p->grid_template, 1);
