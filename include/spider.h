@@ -97,7 +97,10 @@ typedef struct {
                          in LDS tiles of 32 x 32 outputs with a halo of T r points, at
                          most 64 points a side (radius 2: 8, radius 3: 5); automatic: the
                          most it allows on grids of up to 2^20 points (where single-step
-                         launches are bound by latency), else one; bit-identical to
+                         launches are bound by latency); larger grids, automatic (and
+                         tile_h 0), without zero taps inside a box: up to eight steps
+                         (radius 1 in fp32; four or two elsewhere, one for the 49-point
+                         box) streamed through registers; else one; bit-identical to
                          single steps;
                        - anything else: one.
                        Larger values are capped at the plan's maximum.  With 0 and

@@ -21,6 +21,8 @@ struct spider_plan_s {
   int band_h = 16;           // output points per band row: 16, or 8 (paired-line bands)
   int row_swap = 0;          // 1: explicit row swap through an LDS copy (ablation)
   int max_time_block = 1;    // deepest fusion this plan supports (paired 16-bit: 4)
+  bool stream = false;       // direct engine, large 2-D grid: time_block steps per launch in registers
+  int stream_h[4] = {};      //   rows per wave of launches of 1, 2, 4 and 8 steps
   int direct_tile = 32;      // direct engine, several steps per launch: output tile side (16 or 32)
   bool line_deep = false;    // 1-D line whose loops run in LDS, many steps per launch
   int ncu = 256;             // compute units of the plan's device

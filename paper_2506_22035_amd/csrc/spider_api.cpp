@@ -16,6 +16,7 @@
 
 #include "spider.h"
 #include "api_internal.h"
+#include "direct_stream.h"
 #include "kernels.h"
 #include "planner.h"
 
@@ -55,11 +56,7 @@ size_t dtype_bytes(int dt) {
 // fills every CU once (all waves resident, no tail round), but not fewer than
 // 16 rows so the 2r halo rows stay a small fraction of the streamed rows.
 static int auto_tile_h_2d(const spider_plan_s* p) {
-  int dev = 0, ncu = 256;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) == hipSuccess) ncu = prop.multiProcessorCount;
-  }
+  const int ncu = p->ncu;
   int per_cu = p->band_h == 8 && p->carry == SPIDER_F32
                    ? band2d_pair_f32_blocks_per_cu(p->r, p->operand, p->engine, p->split == 3, 1)
                : p->band_h == 8        ? band2d_pair_blocks_per_cu(p->r, p->operand, p->engine)
@@ -80,11 +77,7 @@ static int auto_tile_h_2d(const spider_plan_s* p) {
 // Blocks per wave of the 1-D band kernel: one resident round of waves, at least 8
 // blocks (the staging depth) per wave.
 static int auto_tile_h_1d(const spider_plan_s* p) {
-  int dev = 0, ncu = 256;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) == hipSuccess) ncu = prop.multiProcessorCount;
-  }
+  const int ncu = p->ncu;
   const long long slots = (long long)ncu * 16;
   const long long nblk = (p->nx + 8 + kStripW - 1) / kStripW;
   return (int)std::max<long long>(8, (nblk + slots - 1) / slots);
@@ -93,11 +86,7 @@ static int auto_tile_h_1d(const spider_plan_s* p) {
 // Planes per wave segment of the 3-D band kernel: one resident round over
 // (strip, 4-line y block, z segment) work units, at least 8 planes deep.
 static int auto_tile_h_3d(const spider_plan_s* p) {
-  int dev = 0, ncu = 256;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) == hipSuccess) ncu = prop.multiProcessorCount;
-  }
+  const int ncu = p->ncu;
   int per_cu = p->carry == SPIDER_F32
                    ? band3d_f32_blocks_per_cu(p->r, p->operand, p->engine, p->split == 3, p->rowmask)
                    : band3d_blocks_per_cu(p->r, p->operand, p->engine, p->nx % 8 == 0, p->rowmask);
@@ -113,6 +102,9 @@ static int auto_tile_h_3d(const spider_plan_s* p) {
   h = std::min<long long>(h, p->nz);
   return (int)h;
 }
+
+// Grids from this size on advance several steps per streaming launch.
+constexpr long long kDirectStreamDeepPoints = (1LL << 20) + (1LL << 17);
 
 static int auto_tile_h_direct(const spider_plan_s* p) {
   if (p->ndim == 3) return std::min(p->nz, 32);
@@ -279,11 +271,7 @@ void set_tile2(spider_plan_s* p, int h) {
 // Segment height of the fused kernel: one resident round, at least 32 rows
 // (its halo is 2 T r lines).
 static int auto_tile_h_tb2(const spider_plan_s* p) {
-  int dev = 0, ncu = 256;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) == hipSuccess) ncu = prop.multiProcessorCount;
-  }
+  const int ncu = p->ncu;
   if (p->ndim == 1) {
     // at least 16 output blocks per wave (each wave also reads 2 (T - 1) halo
     // blocks), and no more waves than the fused kernel keeps resident: a second
@@ -391,6 +379,18 @@ struct LoopShape {
   int total;    // then single steps up to k = total
   int rem = 0;  // direct engine, deep: steps of the remainder launch
   int deep = 0;
+  // Large 2-D grids on the direct engine: `fused` launches of time_block steps (a power
+  // of two), then one launch per set bit of rem, the largest first.
+  bool stream = false;
+  int stream_steps(int k, int T) const {
+    if (k <= fused) return T;
+    int b = rem;
+    for (int i = fused + 1;; ++i) {
+      const int top = 1 << (31 - __builtin_clz((unsigned)b));
+      if (i == k) return top;
+      b -= top;
+    }
+  }
   int kind(int k) const { return k <= fused ? 3 : (k <= fused + two ? 2 : 1); }
   int run_end(int k) const { return k <= fused ? fused : (k <= fused + two ? fused + two : total); }
 };
@@ -412,6 +412,14 @@ static LoopShape loop_launches(const spider_plan_s* p, int steps) {
     L.total = L.fused + L.two;
     return L;
   }
+  if (p->stream) {
+    L.stream = true;
+    L.fused = steps / tb;
+    L.rem = steps - tb * L.fused;
+    L.two = 0;
+    L.total = L.fused + __builtin_popcount((unsigned)L.rem);
+    return L;
+  }
   if (p->engine == SPIDER_ENGINE_DIRECT && tb >= 2) {
     L.fused = steps / tb;
     L.rem = steps - tb * L.fused;
@@ -424,6 +432,15 @@ static LoopShape loop_launches(const spider_plan_s* p, int steps) {
   L.two = tb > 2 ? rem / 2 : 0;
   L.total = L.fused + L.two + (rem - 2 * L.two);
   return L;
+}
+
+// `steps` steps (1, 2, 4 or 8) of a direct-engine plan in one launch that streams
+// lines through registers.
+static spider_status launch_stream_steps(spider_plan_s* p, const void* src, void* dst, int steps, hipStream_t s) {
+  const hipError_t e = launch_direct2d_stream(p->r, p->carry == SPIDER_F64 ? 0 : 1, p->star ? 2 : 0, steps, src, dst, p->ny,
+                                              p->nx, p->d_coeffs, p->stream_h[__builtin_ctz((unsigned)steps)], s);
+  if (e != hipSuccess) return hip_fail(e, "kernel launch");
+  return SPIDER_OK;
 }
 
 // `steps` steps of a line in one launch in LDS.  A 16-bit grid with split 3 is
@@ -452,7 +469,8 @@ static spider_status enqueue_launches(spider_plan_s* p, const void* src, void* o
     void* dst = ((L.total - k) % 2 == 0) ? out : scratch;
     if (dst == src) return fail(SPIDER_ERR_INVALID, "internal: launch %d reads and writes one buffer", k);
     const int kind = L.kind(k);
-    spider_status st = L.deep      ? launch_line_steps(p, src, dst, kind == 3 ? L.deep : L.rem, s)
+    spider_status st = L.stream    ? launch_stream_steps(p, src, dst, L.stream_steps(k, p->time_block), s)
+                       : L.deep    ? launch_line_steps(p, src, dst, kind == 3 ? L.deep : L.rem, s)
                        : kind == 3 ? launch_step2(p, src, dst, s)
                        : kind == 2 ? (p->engine == SPIDER_ENGINE_DIRECT ? launch_direct_steps(p, src, dst, L.rem, s)
                                                                         : launch_rem2(p, src, dst, s))
@@ -710,16 +728,26 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     const int maxT = ndim == 2 ? direct2d_fused_max_steps(radius, p->carry == SPIDER_F64 ? 0 : 1) : 1;
     p->max_time_block = maxT >= 2 ? maxT : 1;
     const long long pts2 = (long long)p->ny * p->nx;
-    const int Td = o.time_block ? o.time_block : (pts2 <= kDirectFusedMaxPoints ? p->max_time_block : 1);
+    // larger grids stream lines through registers, several steps per launch (the grids
+    // just above the tile kernel's range one: a plan of 1024 x 1025 points is one of
+    // single steps)
+    const int zt = p->star ? 2 : (p->has_zero_tap ? 1 : 0);
+    int st = ndim == 2 && o.time_block == 0 && o.tile_h == 0 && pts2 > kDirectFusedMaxPoints
+                 ? direct2d_stream_max_steps(radius, p->carry == SPIDER_F64 ? 0 : 1, zt, pts2)
+                 : 0;
+    if (st > 1 && pts2 < kDirectStreamDeepPoints) st = 1;
+    if (st) {
+      p->stream = true;
+      p->max_time_block = st;
+      for (int i = 0; 1 << i <= st; ++i) p->stream_h[i] = direct2d_stream_rows(radius, 1 << i, p->ny, p->nx, p->ncu);
+    }
+    const int Td = p->stream ? p->max_time_block : o.time_block ? o.time_block : (pts2 <= kDirectFusedMaxPoints ? p->max_time_block : 1);
     p->time_block = std::max(1, std::min(Td, p->max_time_block));
     // 16-point tiles where 32-point ones would leave CUs idle (more halo work, but
     // spread over more CUs: each step's time is one tile's LDS traffic)
     {
-      int ncu = 256;
-      hipDeviceProp_t prop;
-      if (hipGetDeviceProperties(&prop, p->device) == hipSuccess) ncu = prop.multiProcessorCount;
       const long long tiles32 = (long long)((p->ny + 31) / 32) * ((p->nx + 31) / 32);
-      p->direct_tile = tiles32 < ncu ? 16 : 32;
+      p->direct_tile = tiles32 < p->ncu ? 16 : 32;
     }
   } else {
     // Offline transformation, one kernel row (line of taps along x) at a time, or
@@ -815,7 +843,7 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     }
     set_time_block(p, std::min(T, p->max_time_block), o.tile_h);
   }
-  if (o.autotune && o.tile_h == 0 && !p->line_deep) {
+  if (o.autotune && o.tile_h == 0 && !p->line_deep && !p->stream) {
     spider_status st = ensure_scratch(p);
     if (st == SPIDER_OK) st = autotune_tile(p);
     if (st != SPIDER_OK) {
