@@ -141,6 +141,39 @@ __device__ __forceinline__ void store_chunk_lds(uint32_t* lds, int off, u32x4 v)
   *reinterpret_cast<uint2*>(lds + off + 2) = make_uint2(v.z, v.w);
 }
 
+// Rows of a 16-bit grid whose width is not a multiple of 8 start and end anywhere.
+// Wide accesses need no more than 2-byte alignment, and the range check of a buffer
+// access works dword by dword, so a 16-byte piece that straddles the end of its
+// line reads (or writes) the dwords inside and zeros (or nothing) beyond; only the
+// last element of a line of odd width is lost, the low half of a dword that ends
+// outside.  Lane 63, which stages no chunk, loads the dword that ends with that
+// element and puts it into the staged row behind its chunk.  (Eight 2-byte loads
+// per chunk instead: Star-2D13P, bf16, 1021 x 1533, 27 us per two-step launch
+// against 10 on an even width.)  Only the waves that hold the end of the lines need
+// any of this; the others run the bodies of whole chunks.
+struct OddTail {
+  bool on;   // wave-uniform: the width is odd and its last element is staged here
+  int at;    // that element's place in the staged row (even)
+  __device__ __forceinline__ OddTail(int nx, int x_first, int n)
+      : on((nx & 1) && nx > 1 && nx - 1 >= x_first && nx - 1 < x_first + n), at(nx - 1 - x_first) {}
+  // byte offset of lane 63's load
+  __device__ __forceinline__ uint32_t voff(uint32_t chunk_voff, int lane, int nx) const {
+    return lane == 63 && on ? (uint32_t)(2 * (nx - 2)) : chunk_voff;
+  }
+  // dword: the element's dword in the padded row
+  __device__ __forceinline__ void put(uint32_t* row, int dword, int lane, u32x4 v) const {
+    if (on && lane == 63) *reinterpret_cast<uint16_t*>(row + dword) = (uint16_t)(v.x >> 16);
+  }
+};
+
+// A chunk of a line of any width (a line of one element is half a dword: by itself).
+template <bool ALIGNED>
+__device__ __forceinline__ u32x4 load_row_chunk(__amdgpu_buffer_rsrc_t rs, uint32_t voff, int nx) {
+  if constexpr (!ALIGNED)
+    if (nx == 1) return (u32x4){__builtin_amdgcn_raw_buffer_load_b16(rs, voff, 0, 0), 0u, 0u, 0u};
+  return __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0);
+}
+
 // Convert an fp32 accumulator (4 consecutive x of one output line) to the
 // 16-bit carry, rounding to nearest even (two packed conversions).
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -192,9 +225,22 @@ __device__ __forceinline__ void store_packed(__amdgpu_buffer_rsrc_t rs, uint32_t
   }
 }
 
-template <int OP, bool ALIGNED>
-__device__ __forceinline__ void store_out(__amdgpu_buffer_rsrc_t rs, uint32_t voff, f32x4 a) {
-  store_packed<ALIGNED>(rs, voff, pack_out<OP>(a));
+// The same on a line of any width: where the line resource ends inside a dword (odd
+// width; `odd` = 1 + the element's index in its quad, 0 for waves without it), the
+// last element is stored by itself at toff (its lane's; out of range for the others).
+template <bool ALIGNED>
+__device__ __forceinline__ void store_row_packed(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t toff, int odd,
+                                                 uint2 w) {
+  store_packed<true>(rs, voff, w);
+  if constexpr (!ALIGNED)
+    if (odd) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)((odd & 2) ? w.y : w.x), rs, toff, 0, 0);
+}
+// odd and toff of a wave whose lanes hold quads at columns x; [lo, hi): the wave's columns
+__device__ __forceinline__ int odd_store(int nx, int lo, int hi) {
+  return (nx & 1) && nx - 1 >= lo && nx - 1 < hi ? 1 + ((nx - 1) & 2) : 0;
+}
+__device__ __forceinline__ uint32_t odd_store_off(int nx, int x) {
+  return x <= nx - 1 && nx - 1 < x + 4 ? (uint32_t)((nx - 1) * 2) : kOffNone;
 }
 
 // One matrix instruction: acc += A(kernel row) x B(input line).

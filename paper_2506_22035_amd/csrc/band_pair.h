@@ -77,21 +77,49 @@ __device__ __forceinline__ f32x4 pair_mma(f32x4 acc, u32x4 a, u32x4 d0, u32x4 d1
   }
 }
 
-// Store a lane's 4 outputs of an output pair: voff[] are per-element byte offsets
-// from the pair's first line (the lane's line and column folded in), out of range
-// for columns outside the grid.
+// A lane's place in the output pair: byte offset of its 4 outputs from the pair's
+// first line (the lane's line and column folded in), out of range where it stores
+// nothing; on ragged widths the one quad of either line that straddles the end of
+// its line (a whole store would reach into the pair's second line) has an offset of
+// its own.
 template <bool ALIGNED>
-__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rs, const uint32_t* voff, uint2 w) {
-  if constexpr (ALIGNED) {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    __builtin_amdgcn_raw_buffer_store_b64((u32x2){w.x, w.y}, rs, voff[0], 0, kStoreNT);
-  } else {
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(w.x & 0xffff), rs, voff[0], 0, 0);
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(w.x >> 16), rs, voff[1], 0, 0);
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(w.y & 0xffff), rs, voff[2], 0, 0);
-    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(w.y >> 16), rs, voff[3], 0, 0);
+struct PairStore {
+  uint32_t off;
+  bool whole, part;  // this lane stores a whole quad / is the straddling one
+  int rem;  // wave-uniform: elements of the straddling quad, 0 where this wave has none
+  // the lane's column x and line; columns [lo, hi) stored; the wave's quads are at [w0, w0 + 128)
+  __device__ __forceinline__ PairStore(int x, int line_off, int lo, int hi, int nx, int w0, int es) {
+    const bool in = x >= lo && x < hi;
+    whole = in && (ALIGNED || x + 4 <= nx);
+    part = in && !whole;
+    off = ALIGNED && !in ? kOffNone : (uint32_t)((x + line_off) * es);
+    rem = !ALIGNED && (nx & 3) && (nx & ~3) >= w0 && (nx & ~3) < w0 + 128 && (nx & ~3) < hi ? (nx & 3) : 0;
+  }
+  __device__ __forceinline__ uint32_t full_off() const { return ALIGNED || whole ? off : kOffNone; }
+  __device__ __forceinline__ uint32_t part_off() const { return part ? off : kOffNone; }
+};
+
+template <bool ALIGNED>
+__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rs, const PairStore<ALIGNED>& o, uint2 w) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64((u32x2){w.x, w.y}, rs, o.full_off(), 0, kStoreNT);
+  if constexpr (!ALIGNED) {
+    if (o.rem) {
+      if (o.rem & 2) __builtin_amdgcn_raw_buffer_store_b32(w.x, rs, o.part_off(), 0, 0);
+      if (o.rem & 1)
+        __builtin_amdgcn_raw_buffer_store_b16((uint16_t)((o.rem & 2) ? w.y : w.x), rs, o.part_off() + 2 * (o.rem & 2), 0, 0);
+    }
   }
 }
+
+// Strips of `width` columns: every column the wave stages (264 from strip width -
+// lead - kPairWinLead on) lies inside the lines' end.
+__device__ __forceinline__ bool pair_inside(const BandGrid& g, int w, int width, int lead) {
+  return (w % g.nstrips) * width - lead + 260 <= g.nx;
+}
+
+// Dword of element i of a staged line.
+__device__ __forceinline__ int pair_dword(int i) { return 6 * (i >> 3) + ((i >> 1) & 3); }
 
 template <int R, int OP, int ENG, bool ALIGNED>
 __device__ __forceinline__ void band2d_pair_body(const BandGrid& g, int w, uint32_t* lds) {
@@ -128,24 +156,20 @@ __device__ __forceinline__ void band2d_pair_body(const BandGrid& g, int w, uint3
   pair_gather_offsets(lane, &p1, &p2);
   // loads: lane c < 33 holds the 8 inputs at xs - 4 + 8c (half h's chunk n window = data dwords 64h + 4n ..+7)
   const bool stager = lane < kPairChunks;
-  const uint32_t lvoff = stager ? (uint32_t)((xs - kPairWinLead + 8 * lane) * 2) : kOffNone;
+  const OddTail tail(ALIGNED ? 0 : nx, xs - kPairWinLead, 8 * kPairChunks);
+  const uint32_t lvoff =
+      tail.voff(stager ? (uint32_t)((xs - kPairWinLead + 8 * lane) * 2) : kOffNone, lane, nx);
   const int lw = 6 * lane;
   // stores: lane (n, h) holds outputs x = xs + 128 half + 8n + 4 (h & 1) + e of line i + (h >> 1)
   const int xo = xs + 8 * (lane & 15) + 4 * ((lane >> 4) & 1);
   const int line_off = (lane >> 5) * nx;
-  uint32_t ova[4], ovb[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int x = xo + (ALIGNED ? 0 : e);
-    ova[e] = (x >= 0 && x < nx) ? (uint32_t)((x + line_off) * 2) : kOffNone;
-    ovb[e] = (x + 128 < nx) ? (uint32_t)((x + 128 + line_off) * 2) : kOffNone;
-  }
+  const PairStore<ALIGNED> ova(xo, line_off, 0, nx, nx, xs, 2), ovb(xo + 128, line_off, 0, nx, nx, xs + 128, 2);
 
   LineWalk lin(g.in, y0 - R, max(0, y0 - R), min(ny, y0 + hrows + R), nx * 2);
   PairWalk pout(g.out, y0 - 2 * R, y0, y0 + hrows, nx * 2);
   u32x4 stg[NL];
 #pragma unroll
-  for (int l = 0; l < NL; ++l) stg[l] = load_chunk<ALIGNED>(lin.next(), lvoff);
+  for (int l = 0; l < NL; ++l) stg[l] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
   f32x4 acc_a[NP], acc_b[NP];
 #pragma unroll
   for (int s = 0; s < NP; ++s) acc_a[s] = acc_b[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -157,6 +181,10 @@ __device__ __forceinline__ void band2d_pair_body(const BandGrid& g, int w, uint3
 #pragma unroll
       for (int l = 0; l < NL; ++l) store_chunk_lds(lds, lw + l * kPairRowDw, stg[l]);
     }
+    if constexpr (!ALIGNED) {
+#pragma unroll
+      for (int l = 0; l < NL; ++l) tail.put(lds + l * kPairRowDw, pair_dword(tail.at), lane, stg[l]);
+    }
     if (b > 0) {
 #pragma unroll
       for (int q = 0; q < UP; ++q) {
@@ -166,7 +194,7 @@ __device__ __forceinline__ void band2d_pair_body(const BandGrid& g, int w, uint3
       }
     }
 #pragma unroll
-    for (int l = 0; l < NL; ++l) stg[l] = load_chunk<ALIGNED>(lin.next(), lvoff);
+    for (int l = 0; l < NL; ++l) stg[l] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
     wave_lds_sync();
 #pragma unroll
     for (int q = 0; q < UP; ++q) {
@@ -259,7 +287,9 @@ __device__ __forceinline__ void band2d_pair_tb2_body(const BandGrid& g, int w, u
   int p1, p2;
   pair_gather_offsets(lane, &p1, &p2);
   const bool stager = lane < kPairChunks;
-  const uint32_t lvoff = stager ? (uint32_t)((xp - kPairWinLead + 8 * lane) * 2) : kOffNone;
+  const OddTail tail(ALIGNED ? 0 : nx, xp - kPairWinLead, 8 * kPairChunks);
+  const uint32_t lvoff =
+      tail.voff(stager ? (uint32_t)((xp - kPairWinLead + 8 * lane) * 2) : kOffNone, lane, nx);
   const int lw = 6 * lane;
   // this lane's 4 values of either pass: columns xo + e (half a) and xo + 128 + e (half b)
   // of line 2m + (lane >> 5) of the pair
@@ -267,13 +297,10 @@ __device__ __forceinline__ void band2d_pair_tb2_body(const BandGrid& g, int w, u
   const int phi = lane >> 5;
   const int line_off = phi * nx;
   const int x_lo = strip * kStripWPair2, x_hi = min(nx, x_lo + kStripWPair2);  // stored columns
-  uint32_t ova[4], ovb[4];
+  const PairStore<ALIGNED> ova(xo, line_off, x_lo, x_hi, nx, xp, 2), ovb(xo + 128, line_off, x_lo, x_hi, nx, xp + 128, 2);
   uint32_t ma0 = 0, ma1 = 0, mb0 = 0, mb1 = 0;  // 16-bit lanes of the intermediate values inside the grid
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int xa = xo + (ALIGNED ? 0 : e), xb = xa + 128;
-    ova[e] = (xa >= x_lo && xa < x_hi) ? (uint32_t)((xa + line_off) * 2) : kOffNone;
-    ovb[e] = (xb >= x_lo && xb < x_hi) ? (uint32_t)((xb + line_off) * 2) : kOffNone;
     const uint32_t half = (e & 1) ? 0xffff0000u : 0x0000ffffu;
     const int ya = xo + e, yb = xo + 128 + e;
     if (ya >= 0 && ya < nx) (e < 2 ? ma0 : ma1) |= half;
@@ -289,7 +316,7 @@ __device__ __forceinline__ void band2d_pair_tb2_body(const BandGrid& g, int w, u
   PairWalk pout(g.out, y0 - 2 * (2 * R + 1), y0, y0 + hrows, nx * 2);
   u32x4 stg[NL];
 #pragma unroll
-  for (int l = 0; l < NL; ++l) stg[l] = load_chunk<ALIGNED>(lin.next(), lvoff);
+  for (int l = 0; l < NL; ++l) stg[l] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
   f32x4 a1[NP], b1[NP], a2[NP], b2[NP];
 #pragma unroll
   for (int s = 0; s < NP; ++s) a1[s] = b1[s] = a2[s] = b2[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -303,6 +330,10 @@ __device__ __forceinline__ void band2d_pair_tb2_body(const BandGrid& g, int w, u
 #pragma unroll
       for (int l = 0; l < NL; ++l) store_chunk_lds(lds, lw + l * kPairRowDw, stg[l]);
     }
+    if constexpr (!ALIGNED) {
+#pragma unroll
+      for (int l = 0; l < NL; ++l) tail.put(lds + l * kPairRowDw, pair_dword(tail.at), lane, stg[l]);
+    }
     if (b > 0) {
 #pragma unroll
       for (int q = 0; q < UP; ++q) {
@@ -312,7 +343,7 @@ __device__ __forceinline__ void band2d_pair_tb2_body(const BandGrid& g, int w, u
       }
     }
 #pragma unroll
-    for (int l = 0; l < NL; ++l) stg[l] = load_chunk<ALIGNED>(lin.next(), lvoff);
+    for (int l = 0; l < NL; ++l) stg[l] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
 #pragma unroll
     for (int q = 0; q < UP; ++q) {
       const int P = b * UP + q;

@@ -102,8 +102,11 @@ __device__ __forceinline__ void band2d_body(const BandGrid& g, int w, uint32_t* 
   const int xd0 = xn * kXTileStride + xswap_slot(4 * xh), xd1 = xn * kXTileStride + xswap_slot(4 * xh + 1);
   const int xd2 = xn * kXTileStride + xswap_slot(4 * xh + 2), xd3 = xn * kXTileStride + xswap_slot(4 * xh + 3);
   const int xrd = xn * kXTileStride + 4 * xh;
-  const uint32_t lvoff = chunk_voffset(x0, lane);
+  const OddTail tail(ALIGNED ? 0 : nx, x0 - 8, 8 * kRowChunks);
+  const uint32_t lvoff = tail.voff(chunk_voffset(x0, lane), lane, nx);
   const uint32_t ovoff = out_voffset(x0, lane);
+  const int odd = ALIGNED ? 0 : odd_store(nx, x0, x0 + kStripW);
+  const uint32_t ooff = odd_store_off(nx, x0 + 16 * (lane & 15) + 4 * (lane >> 4));
   const int lw = chunk_lds_offset(lane, U * kLdsRowDw);  // lanes >= 34: spare area
   const int lstride = lane < kRowChunks ? kLdsRowDw : 0;
 
@@ -117,7 +120,7 @@ __device__ __forceinline__ void band2d_body(const BandGrid& g, int w, uint32_t* 
   LineWalk lout(g.out, out_row(-2 * R), y0, y0 + hrows, nx * 2);
   u32x4 stg[U];
 #pragma unroll
-  for (int q = 0; q < U; ++q) stg[q] = load_chunk<ALIGNED>(lin.next(), lvoff);
+  for (int q = 0; q < U; ++q) stg[q] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
   f32x4 acc[RR];
 #pragma unroll
   for (int s = 0; s < RR; ++s) acc[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -132,12 +135,16 @@ __device__ __forceinline__ void band2d_body(const BandGrid& g, int w, uint32_t* 
 #pragma unroll
       for (int q = 0; q < U; ++q) store_chunk_lds(lds, lw + q * lstride, stg[q]);
     }
+    if constexpr (!ALIGNED) {
+#pragma unroll
+      for (int q = 0; q < U; ++q) tail.put(lds + q * kLdsRowDw, lds_phys(tail.at >> 1), lane, stg[q]);
+    }
     if (jb > 0) {
 #pragma unroll
-      for (int q = 0; q < U; ++q) store_packed<ALIGNED>(lout.next(), ovoff, done[q]);  // output jb - U + q - 2R
+      for (int q = 0; q < U; ++q) store_row_packed<ALIGNED>(lout.next(), ovoff, ooff, odd, done[q]);  // output jb - U + q - 2R
     }
 #pragma unroll
-    for (int q = 0; q < U; ++q) stg[q] = load_chunk<ALIGNED>(lin.next(), lvoff);  // input jb + U + q
+    for (int q = 0; q < U; ++q) stg[q] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);  // input jb + U + q
     wave_lds_sync();
 #pragma unroll
     for (int q = 0; q < U; ++q) {
@@ -174,20 +181,24 @@ __device__ __forceinline__ void band2d_body(const BandGrid& g, int w, uint32_t* 
     }
   }
 #pragma unroll
-  for (int q = 0; q < U; ++q) store_packed<ALIGNED>(lout.next(), ovoff, done[q]);  // output nin - U + q - 2R
+  for (int q = 0; q < U; ++q) store_row_packed<ALIGNED>(lout.next(), ovoff, ooff, odd, done[q]);  // output nin - U + q - 2R
 }
 
 
 
 template <int R, int OP, int ENG, bool ALIGNED, bool XSWAP = false>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(
-    ENG == 1 ? ((R <= 2 && ALIGNED && !XSWAP) ? 4 : ((R <= 2 || (R == 3 && ALIGNED)) ? 3 : 2))
+    ENG == 1 ? ((R <= 2 && !XSWAP) ? 4 : (R <= 3 ? 3 : 2))
              : (R <= 2 ? 3 : (R <= 4 ? 2 : 1)))))
 void band2d_kernel(BandGrid g) {
   constexpr int kLds = XSWAP ? band2d_xtile_base<R>() + 2 * kXTileDw : band2d_lines<R>() * kLdsRowDw + kLdsSpareDw;
   __shared__ __attribute__((aligned(16))) uint32_t lds[kLds];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  band2d_body<R, OP, ENG, ALIGNED, XSWAP>(g, w, lds);
+  // (only the waves at the end of the lines need the ragged body)
+  if (ALIGNED || (w % g.nstrips) * kStripW + 256 <= g.nx)
+    band2d_body<R, OP, ENG, true, XSWAP>(g, w, lds);
+  else
+    band2d_body<R, OP, ENG, ALIGNED, XSWAP>(g, w, lds);
 }
 
 // ----------------------------------------------------------------------------- 1-D
@@ -760,8 +771,11 @@ __device__ __forceinline__ void band3d_body(const BandGrid& g, int w, uint32_t* 
 
   int p1, p2;
   band_gather_offsets(lane, &p1, &p2);
-  const uint32_t lvoff = chunk_voffset(x0, lane);
+  const OddTail tail(ALIGNED ? 0 : nx, x0 - 8, 8 * kRowChunks);
+  const uint32_t lvoff = tail.voff(chunk_voffset(x0, lane), lane, nx);
   const uint32_t ovoff = out_voffset(x0, lane);
+  const int odd = ALIGNED ? 0 : odd_store(nx, x0, x0 + kStripW);
+  const uint32_t ooff = odd_store_off(nx, x0 + 16 * (lane & 15) + 4 * (lane >> 4));
   const int lw = chunk_lds_offset(lane, NL * kLdsRowDw);
   const int lstride = lane < kRowChunks ? kLdsRowDw : 0;
 
@@ -781,7 +795,7 @@ __device__ __forceinline__ void band3d_body(const BandGrid& g, int w, uint32_t* 
       const bool valid = zv && (uint32_t)(yb0 - R + l) < (uint32_t)ny;
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
           reinterpret_cast<void*>(in_addr + (uint64_t)(l * lb)), (short)0, valid ? lb : 0, kRsrcWord3);
-      stg[l] = load_chunk<ALIGNED>(rs, lvoff);
+      stg[l] = load_row_chunk<ALIGNED>(rs, lvoff, nx);
     }
     in_addr += (uint64_t)pbytes;
     ++zrel;
@@ -794,7 +808,7 @@ __device__ __forceinline__ void band3d_body(const BandGrid& g, int w, uint32_t* 
       const bool ov = k < hz && yb0 + b < ny;
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
           reinterpret_cast<void*>(out_addr + (uint64_t)(b * lb)), (short)0, ov ? lb : 0, kRsrcWord3);
-      store_packed<ALIGNED>(rs, ovoff, vals[b]);
+      store_row_packed<ALIGNED>(rs, ovoff, ooff, odd, vals[b]);
     }
     out_addr += (uint64_t)pbytes;
   };
@@ -815,6 +829,10 @@ __device__ __forceinline__ void band3d_body(const BandGrid& g, int w, uint32_t* 
       if (lane < kRowChunks) {
 #pragma unroll
         for (int l = 0; l < NL; ++l) store_chunk_lds(lds, lw + l * lstride, stg[l]);
+      }
+      if constexpr (!ALIGNED) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) tail.put(lds + l * kLdsRowDw, lds_phys(tail.at >> 1), lane, stg[l]);
       }
       if (done_plane >= 0) store_plane(done_plane, done);
       stage();  // plane pj + 1
@@ -853,11 +871,15 @@ __device__ __forceinline__ void band3d_body(const BandGrid& g, int w, uint32_t* 
 }
 
 template <int R, int OP, int ENG, bool ALIGNED, uint32_t MASK>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((ENG == 1 && ALIGNED) ? 3 : 2))) void band3d_kernel(BandGrid g) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ENG == 1 ? 3 : 2))) void band3d_kernel(BandGrid g) {
   constexpr int NL = kRowsY3 + 2 * R;
   __shared__ uint32_t lds[NL * kLdsRowDw + kLdsSpareDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  band3d_body<R, OP, ENG, ALIGNED, MASK>(g, w, lds);
+  // (only the waves at the end of the lines need the ragged body)
+  if (ALIGNED || (w % g.nstrips) * kStripW + 264 <= g.nx)
+    band3d_body<R, OP, ENG, true, MASK>(g, w, lds);
+  else
+    band3d_body<R, OP, ENG, ALIGNED, MASK>(g, w, lds);
 }
 
 // ----------------------------------------------------------------------------- 3-D, two fused steps
@@ -1223,8 +1245,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(((CLS == 5 |
   }
   const BandGrid g = grids[lo];
   const int w = unit - begin[lo];
-  const bool al = al_only || (g.nx % 8) == 0;
   const int kind = kinds[lo];
+  // whole-chunk bodies: widths that are multiples of 8, and on ragged grids the waves
+  // that stage nothing beyond the end of the lines
+  const int sx = w % g.nstrips;
+  const bool al = al_only || (g.nx % 8) == 0 ||
+                  (kind >= kB2dPairTb2R1 ? sx * kStripWPair2 + 256
+                   : kind >= kB2dPairR1  ? sx * kStripWPair + 256
+                   : kind >= kB3dBox     ? sx * kStripW + 264
+                                         : sx * kStripW + 256) <= g.nx;
   if constexpr (k2d) {
     switch (kind) {
       case kB2dR1: if (al) band2d_body<1, OP, ENG, true>(g, w, lds); else band2d_body<1, OP, ENG, false>(g, w, lds); break;

@@ -672,9 +672,9 @@ hipError_t dispatch_f32(int r, const BandGrid& g, hipStream_t s) {
 
 template <int OP, int ENG>
 hipError_t dispatch_f32_al(int r, bool xlo, const BandGrid& g, hipStream_t s) {
-  const bool al = (g.nx % 4) == 0;
-  if (al) return xlo ? dispatch_f32<OP, ENG, true, true>(r, g, s) : dispatch_f32<OP, ENG, true, false>(r, g, s);
-  return xlo ? dispatch_f32<OP, ENG, false, true>(r, g, s) : dispatch_f32<OP, ENG, false, false>(r, g, s);
+  // 16-byte accesses for any width: the range check works dword by dword, and an
+  // fp32 value is a dword
+  return xlo ? dispatch_f32<OP, ENG, true, true>(r, g, s) : dispatch_f32<OP, ENG, true, false>(r, g, s);
 }
 
 }  // namespace
@@ -699,9 +699,9 @@ hipError_t dispatch3d_f32(const BandGrid& g, hipStream_t s) {
 }
 template <int OP, int ENG>
 hipError_t dispatch3d_f32_al(bool xlo, const BandGrid& g, hipStream_t s) {
-  const bool al = (g.nx % 4) == 0;
-  if (al) return xlo ? dispatch3d_f32<OP, ENG, true, true>(g, s) : dispatch3d_f32<OP, ENG, true, false>(g, s);
-  return xlo ? dispatch3d_f32<OP, ENG, false, true>(g, s) : dispatch3d_f32<OP, ENG, false, false>(g, s);
+  // 16-byte accesses for any width: the range check works dword by dword, and an
+  // fp32 value is a dword
+  return xlo ? dispatch3d_f32<OP, ENG, true, true>(g, s) : dispatch3d_f32<OP, ENG, true, false>(g, s);
 }
 template <int OP, int ENG, bool XLO>
 int occ3d_f32(uint32_t rowmask) {
@@ -735,9 +735,9 @@ hipError_t dispatch1d_f32(int r, const BandGrid& g, hipStream_t s) {
 }
 template <int OP, int ENG>
 hipError_t dispatch1d_f32_al(int r, bool xlo, const BandGrid& g, hipStream_t s) {
-  const bool al = (g.nx % 4) == 0;
-  if (al) return xlo ? dispatch1d_f32<OP, ENG, true, true>(r, g, s) : dispatch1d_f32<OP, ENG, true, false>(r, g, s);
-  return xlo ? dispatch1d_f32<OP, ENG, false, true>(r, g, s) : dispatch1d_f32<OP, ENG, false, false>(r, g, s);
+  // 16-byte accesses for any width: the range check works dword by dword, and an
+  // fp32 value is a dword
+  return xlo ? dispatch1d_f32<OP, ENG, true, true>(r, g, s) : dispatch1d_f32<OP, ENG, true, false>(r, g, s);
 }
 }  // namespace
 

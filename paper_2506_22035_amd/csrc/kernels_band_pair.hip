@@ -24,31 +24,36 @@
 
 namespace spider_impl {
 
+// ALIGNED = false: widths that are not a multiple of 8; only the waves that stage the
+// end of the lines run the ragged bodies.
 template <int R, int OP, int ENG, bool ALIGNED>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ALIGNED ? 4 : (ENG == 1 ? 3 : 2)))) void band2d_pair_kernel(BandGrid g) {
   constexpr int NP = R + 1;
   constexpr int UP = (NP >= 3) ? NP : 2 * NP;
   __shared__ uint32_t lds[2 * UP * kPairRowDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  band2d_pair_body<R, OP, ENG, ALIGNED>(g, w, lds);
+  if (ALIGNED || pair_inside(g, w, kStripWPair, kPairWinLead))
+    band2d_pair_body<R, OP, ENG, true>(g, w, lds);
+  else
+    band2d_pair_body<R, OP, ENG, ALIGNED>(g, w, lds);
 }
 
 // ----------------------------------------------------------------------------- two fused steps
 // (the body, band2d_pair_tb2_body, is in band_pair.h: batched launches run it too)
 template <int R, int OP, int ENG, bool ALIGNED>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((ENG == 1 && ALIGNED) ? 3 : 2))) void band2d_pair_tb2_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ENG == 1 ? 3 : 2))) void band2d_pair_tb2_kernel(
     BandGrid g) {
   constexpr int NP = R + 1;
   constexpr int UP = (NP >= 3) ? NP : 2 * NP;
   __shared__ uint32_t lds[(2 * UP + 4) * kPairRowDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  if constexpr (ENG == 1 && ALIGNED) {  // (a second body would spill the other variants)
+  if constexpr (ENG == 1) {  // (a second body would spill the dense variants)
     // interior waves: columns [xp, xp + 256) and rows [y0 - 2R, y0 + hrows + 2R + 2) inside the grid
     const int strip = w % g.nstrips, seg = w / g.nstrips;
     const int xp = strip * kStripWPair2 - kPairWinLead;
     const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
-    if (xp >= 0 && xp + 256 <= g.nx && y0 - 2 * R >= 0 && y0 + hrows + 2 * R + 2 <= g.ny) {
-      band2d_pair_tb2_body<R, OP, ENG, ALIGNED, false>(g, w, lds);
+    if (xp >= 0 && xp + (ALIGNED ? 256 : 260) <= g.nx && y0 - 2 * R >= 0 && y0 + hrows + 2 * R + 2 <= g.ny) {
+      band2d_pair_tb2_body<R, OP, ENG, true, false>(g, w, lds);
       return;
     }
   }
@@ -103,7 +108,9 @@ __device__ __forceinline__ void band2d_pair_tbt_body(const BandGrid& g, int w, u
   int p1, p2;
   pair_gather_offsets(lane, &p1, &p2);
   const bool stager = lane < kPairChunks;
-  const uint32_t lvoff = stager ? (uint32_t)((xp - kPairWinLead + 8 * lane) * 2) : kOffNone;
+  const OddTail tail(ALIGNED ? 0 : nx, xp - kPairWinLead, 8 * kPairChunks);
+  const uint32_t lvoff =
+      tail.voff(stager ? (uint32_t)((xp - kPairWinLead + 8 * lane) * 2) : kOffNone, lane, nx);
   const int lw = 6 * lane;
   // this lane's 4 values of every pass: columns xo + e (half a) and xo + 128 + e (half b)
   // of line 2m + (lane >> 5) of the pair
@@ -111,13 +118,10 @@ __device__ __forceinline__ void band2d_pair_tbt_body(const BandGrid& g, int w, u
   const int phi = lane >> 5;
   const int line_off = phi * nx;
   const int x_hi = min(nx, x_lo + WIDTH);  // stored columns [x_lo, x_hi)
-  uint32_t ova[4], ovb[4];
+  const PairStore<ALIGNED> ova(xo, line_off, x_lo, x_hi, nx, xp, 2), ovb(xo + 128, line_off, x_lo, x_hi, nx, xp + 128, 2);
   uint32_t ma0 = 0, ma1 = 0, mb0 = 0, mb1 = 0;  // 16-bit lanes of the intermediate values inside the grid
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int xa = xo + (ALIGNED ? 0 : e), xb = xa + 128;
-    ova[e] = (xa >= x_lo && xa < x_hi) ? (uint32_t)((xa + line_off) * 2) : kOffNone;
-    ovb[e] = (xb >= x_lo && xb < x_hi) ? (uint32_t)((xb + line_off) * 2) : kOffNone;
     const uint32_t half = (e & 1) ? 0xffff0000u : 0x0000ffffu;
     const int ya = xo + e, yb = xo + 128 + e;
     if (ya >= 0 && ya < nx) (e < 2 ? ma0 : ma1) |= half;
@@ -134,7 +138,7 @@ __device__ __forceinline__ void band2d_pair_tbt_body(const BandGrid& g, int w, u
   PairWalk pout(g.out, y0 - 2 * ((T - 1) * (R + 1) + R), y0, y0 + hrows, nx * 2);
   u32x4 stg[NL];
 #pragma unroll
-  for (int l = 0; l < NL; ++l) stg[l] = load_chunk<ALIGNED>(lin.next(), lvoff);
+  for (int l = 0; l < NL; ++l) stg[l] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
   f32x4 acc_a[T][NP], acc_b[T][NP];
 #pragma unroll
   for (int t = 0; t < T; ++t)
@@ -148,6 +152,10 @@ __device__ __forceinline__ void band2d_pair_tbt_body(const BandGrid& g, int w, u
 #pragma unroll
       for (int l = 0; l < NL; ++l) store_chunk_lds(lds, lw + l * kPairRowDw, stg[l]);
     }
+    if constexpr (!ALIGNED) {
+#pragma unroll
+      for (int l = 0; l < NL; ++l) tail.put(lds + l * kPairRowDw, pair_dword(tail.at), lane, stg[l]);
+    }
     if (b > 0) {
 #pragma unroll
       for (int q = 0; q < UP; ++q) {
@@ -157,7 +165,7 @@ __device__ __forceinline__ void band2d_pair_tbt_body(const BandGrid& g, int w, u
       }
     }
 #pragma unroll
-    for (int l = 0; l < NL; ++l) stg[l] = load_chunk<ALIGNED>(lin.next(), lvoff);
+    for (int l = 0; l < NL; ++l) stg[l] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
 #pragma unroll
     for (int q = 0; q < UP; ++q) {
       const int P = b * UP + q;
@@ -252,11 +260,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ba
   const int strip = w % g.nstrips, seg = w / g.nstrips;
   const int xp = strip * pair_tb_width(T, R) - pair_tb_margin(T, R);
   const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
-  const bool interior = xp >= 0 && xp + 256 <= g.nx && y0 - T * R >= 0 && y0 + hrows + T * R + 2 <= g.ny;
+  const bool interior = xp >= 0 && xp + (ALIGNED ? 256 : 260) <= g.nx && y0 - T * R >= 0 && y0 + hrows + T * R + 2 <= g.ny;
   (void)interior;
   if constexpr (ENG == 1) {
     if (interior) {
-      band2d_pair_tbt_body<R, OP, ENG, ALIGNED, T, false>(g, w, lds);
+      band2d_pair_tbt_body<R, OP, ENG, true, T, false>(g, w, lds);
       return;
     }
   }

@@ -31,17 +31,10 @@ struct PairF32Line {
   uint32_t t;
 };
 
-template <bool ALIGNED>
+// (any width: the range check works dword by dword)
 __device__ __forceinline__ PairF32Line load_pair_f32(__amdgpu_buffer_rsrc_t rs, uint32_t mvoff, uint32_t tvoff) {
   PairF32Line L;
-  if constexpr (ALIGNED) {
-    L.m = __builtin_amdgcn_raw_buffer_load_b128(rs, mvoff, 0, 0);
-  } else {
-    L.m = (u32x4){__builtin_amdgcn_raw_buffer_load_b32(rs, mvoff, 0, 0),
-                  __builtin_amdgcn_raw_buffer_load_b32(rs, mvoff + 4, 0, 0),
-                  __builtin_amdgcn_raw_buffer_load_b32(rs, mvoff + 8, 0, 0),
-                  __builtin_amdgcn_raw_buffer_load_b32(rs, mvoff + 12, 0, 0)};
-  }
+  L.m = __builtin_amdgcn_raw_buffer_load_b128(rs, mvoff, 0, 0);
   L.t = __builtin_amdgcn_raw_buffer_load_b32(rs, tvoff, 0, 0);
   return L;
 }
@@ -78,18 +71,19 @@ __device__ __forceinline__ void stage_pair_f32(uint32_t* hi, uint32_t* lo, int l
   }
 }
 
-// Store a lane's 4 fp32 outputs: voff[] are per-element byte offsets from the
-// pair's first line, out of range where the output is not stored.
+// Store a lane's 4 fp32 outputs of an output pair.
 template <bool ALIGNED>
-__device__ __forceinline__ void store_pair_f32(__amdgpu_buffer_rsrc_t rs, const uint32_t* voff, f32x4 v) {
+__device__ __forceinline__ void store_pair_f32(__amdgpu_buffer_rsrc_t rs, const PairStore<ALIGNED>& o, f32x4 v) {
+  // whole-vector cast: element-wise casts feeding these stores have been seen to
+  // compile to four stores of element 0
   const u32x4 u = __builtin_bit_cast(u32x4, v);
-  if constexpr (ALIGNED) {
-    __builtin_amdgcn_raw_buffer_store_b128(u, rs, voff[0], 0, kStoreNT);
-  } else {
-    // whole-vector cast first: element-wise casts feeding these stores have
-    // been seen to compile to four stores of element 0
+  __builtin_amdgcn_raw_buffer_store_b128(u, rs, o.full_off(), 0, kStoreNT);
+  if constexpr (!ALIGNED) {
+    if (o.rem) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) __builtin_amdgcn_raw_buffer_store_b32(u[t], rs, voff[t], 0, 0);
+      for (int t = 0; t < 3; ++t)
+        if (t < o.rem) __builtin_amdgcn_raw_buffer_store_b32(u[t], rs, o.part_off() + 4 * t, 0, 0);
+    }
   }
 }
 
@@ -156,13 +150,10 @@ __device__ __forceinline__ void band2d_pair_f32_body12(const BandGrid& g, int w,
   const int line_off = phi * nx;
   const int x_lo = FUSED ? strip * kStripWPair2 : 0;
   const int x_hi = FUSED ? min(nx, x_lo + kStripWPair2) : nx;
-  uint32_t ova[4], ovb[4];
+  const PairStore<ALIGNED> ova(xo, line_off, x_lo, x_hi, nx, xp, 4), ovb(xo + 128, line_off, x_lo, x_hi, nx, xp + 128, 4);
   uint32_t ma[4], mb[4];  // intermediate values inside the grid (fused only)
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int xa = xo + (ALIGNED ? 0 : e), xb = xa + 128;
-    ova[e] = (xa >= x_lo && xa < x_hi) ? (uint32_t)((xa + line_off) * 4) : kOffNone;
-    ovb[e] = (xb >= x_lo && xb < x_hi) ? (uint32_t)((xb + line_off) * 4) : kOffNone;
     ma[e] = (xo + e >= 0 && xo + e < nx) ? 0xffffffffu : 0u;
     mb[e] = (xo + 128 + e < nx) ? 0xffffffffu : 0u;
   }
@@ -180,7 +171,7 @@ __device__ __forceinline__ void band2d_pair_f32_body12(const BandGrid& g, int w,
   PairWalk pout(g.out, FUSED ? y0 - 2 * (2 * R + 1) : y0 - 2 * R, y0, y0 + hrows, nx * 4);
   PairF32Line stg[2 * UP];
 #pragma unroll
-  for (int l = 0; l < 2 * UP; ++l) stg[l] = load_pair_f32<ALIGNED>(lin.next(), mvoff, tvoff);
+  for (int l = 0; l < 2 * UP; ++l) stg[l] = load_pair_f32(lin.next(), mvoff, tvoff);
   f32x4 a1[NP], b1[NP], a2[FUSED ? NP : 1], b2[FUSED ? NP : 1];
 #pragma unroll
   for (int s = 0; s < NP; ++s) a1[s] = b1[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -199,8 +190,8 @@ __device__ __forceinline__ void band2d_pair_f32_body12(const BandGrid& g, int w,
       // input pair P: hi lines at 0 / LINE, lo lines at 2 LINE / 3 LINE
       stage_pair_f32<OP, XLO>(slot_in, slot_in + 2 * LINE, lane, mw, tw, stg[2 * q]);
       stage_pair_f32<OP, XLO>(slot_in + LINE, slot_in + 3 * LINE, lane, mw, tw, stg[2 * q + 1]);
-      stg[2 * q] = load_pair_f32<ALIGNED>(lin.next(), mvoff, tvoff);  // input pair P + UP
-      stg[2 * q + 1] = load_pair_f32<ALIGNED>(lin.next(), mvoff, tvoff);
+      stg[2 * q] = load_pair_f32(lin.next(), mvoff, tvoff);  // input pair P + UP
+      stg[2 * q + 1] = load_pair_f32(lin.next(), mvoff, tvoff);
       wave_lds_sync();
       {
         const uint32_t* h0 = slot_in;
@@ -332,13 +323,10 @@ __device__ __forceinline__ void band2d_pair_f32_bodyT(const BandGrid& g, int w, 
   const int phi = lane >> 5;
   const int line_off = phi * nx;
   const int x_lo = strip * W, x_hi = min(nx, x_lo + W);  // stored columns
-  uint32_t ova[4], ovb[4];
+  const PairStore<ALIGNED> ova(xo, line_off, x_lo, x_hi, nx, xp, 4), ovb(xo + 128, line_off, x_lo, x_hi, nx, xp + 128, 4);
   uint32_t ma[4], mb[4];  // intermediate values inside the grid (fused only)
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int xa = xo + (ALIGNED ? 0 : e), xb = xa + 128;
-    ova[e] = (xa >= x_lo && xa < x_hi) ? (uint32_t)((xa + line_off) * 4) : kOffNone;
-    ovb[e] = (xb >= x_lo && xb < x_hi) ? (uint32_t)((xb + line_off) * 4) : kOffNone;
     ma[e] = (xo + e >= 0 && xo + e < nx) ? 0xffffffffu : 0u;
     mb[e] = (xo + 128 + e < nx) ? 0xffffffffu : 0u;
   }
@@ -355,7 +343,7 @@ __device__ __forceinline__ void band2d_pair_f32_bodyT(const BandGrid& g, int w, 
   PairWalk pout(g.out, y0 - 2 * ((T - 1) * (R + 1) + R), y0, y0 + hrows, nx * 4);
   PairF32Line stg[2 * UP];
 #pragma unroll
-  for (int l = 0; l < 2 * UP; ++l) stg[l] = load_pair_f32<ALIGNED>(lin.next(), mvoff, tvoff);
+  for (int l = 0; l < 2 * UP; ++l) stg[l] = load_pair_f32(lin.next(), mvoff, tvoff);
   f32x4 acc_a[T][NP], acc_b[T][NP];
 #pragma unroll
   for (int t = 0; t < T; ++t)
@@ -371,8 +359,8 @@ __device__ __forceinline__ void band2d_pair_f32_bodyT(const BandGrid& g, int w, 
       // input pair P: hi lines at 0 / LINE, lo lines at 2 LINE / 3 LINE
       stage_pair_f32<OP, XLO>(slot_in, slot_in + 2 * LINE, lane, mw, tw, stg[2 * q]);
       stage_pair_f32<OP, XLO>(slot_in + LINE, slot_in + 3 * LINE, lane, mw, tw, stg[2 * q + 1]);
-      stg[2 * q] = load_pair_f32<ALIGNED>(lin.next(), mvoff, tvoff);  // input pair P + UP
-      stg[2 * q + 1] = load_pair_f32<ALIGNED>(lin.next(), mvoff, tvoff);
+      stg[2 * q] = load_pair_f32(lin.next(), mvoff, tvoff);  // input pair P + UP
+      stg[2 * q + 1] = load_pair_f32(lin.next(), mvoff, tvoff);
       wave_lds_sync();
 #pragma unroll
       for (int t = 0; t < T; ++t) {
@@ -449,7 +437,11 @@ void band2d_pair_f32_kernel(BandGrid g) {
   __shared__ uint32_t lds[2 * T * PAIRSZ];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
   if constexpr (T <= 2) {
-    band2d_pair_f32_body12<R, OP, ENG, ALIGNED, XLO, T == 2>(g, w, lds);
+    // (only the waves at the end of the lines need the ragged stores)
+    if (ALIGNED || pair_inside(g, w, T == 2 ? kStripWPair2 : kStripWPair, kPairWinLead))
+      band2d_pair_f32_body12<R, OP, ENG, true, XLO, T == 2>(g, w, lds);
+    else
+      band2d_pair_f32_body12<R, OP, ENG, ALIGNED, XLO, T == 2>(g, w, lds);
   } else {
     // interior waves (columns [xp, xp + 256) and rows [y0 - T r, y0 + hrows + T r + 2)
     // inside the grid) skip the zeroing of intermediate values outside it
@@ -457,7 +449,7 @@ void band2d_pair_f32_kernel(BandGrid g) {
     const int xp = strip * pair_tb_width(T, R) - pair_tb_margin(T, R);
     const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
     if (xp >= 0 && xp + 256 <= g.nx && y0 - T * R >= 0 && y0 + hrows + T * R + 2 <= g.ny)
-      band2d_pair_f32_bodyT<R, OP, ENG, ALIGNED, XLO, T, false>(g, w, lds);
+      band2d_pair_f32_bodyT<R, OP, ENG, true, XLO, T, false>(g, w, lds);
     else
       band2d_pair_f32_bodyT<R, OP, ENG, ALIGNED, XLO, T, true>(g, w, lds);
   }
