@@ -14,8 +14,7 @@ __device__ __forceinline__ void split2(uint32_t a, uint32_t b, uint32_t* hi, uin
   *hi = pack2<OP>(fa, fb);
   if constexpr (XLO) {
     const f32x2 h = unpack2<OP>(*hi);
-    // x - hi is exact, so the fused form (one instruction with the 16-bit operand) is the same
-    *lo = pack2<OP>(__builtin_fmaf(h.x, -1.0f, fa), __builtin_fmaf(h.y, -1.0f, fb));
+    *lo = pack2<OP>(fa - h.x, fb - h.y);
   } else {
     *lo = 0u;
   }

@@ -4,6 +4,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "band_common.h"
 #include "kernels.h"
 
@@ -425,6 +427,295 @@ __device__ __forceinline__ void band2d_pair_tb2_body(const BandGrid& g, int w, u
     store_pair<ALIGNED>(rs, ova, done_a[q]);
     store_pair<ALIGNED>(rs, ovb, done_b[q]);
   }
+}
+
+// ----------------------------------------------------------------------------- odd radii: four input lines
+// One sparse instruction on four input lines, two consecutive pairs, one copy of
+// each line's window per lane half (the planner's pack_quad).  Compared with a hi
+// and a lo copy of two lines in K, every line pair is gathered once instead of
+// twice, the operand of pair j (registers of the older pair kept, those of the one
+// before it replaced) is ready before the matrix instructions start, and only
+// (r - 1) / 2 + 1 output pairs per level are in flight instead of r + 1: MEASURED
+
+// The coefficient operands: instruction k for operands whose lower half is the older
+// pair (a[0]) or the newer one (a[1]: the same with its K halves exchanged).
+template <int R>
+struct QuadA {
+  u32x4 a[2][R + 1];
+  uint32_t i[2][(R + 1) / 2];
+  __device__ __forceinline__ void load(const BandGrid& g, int lane) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const int la = lane ^ (32 * v);
+#pragma unroll
+      for (int k = 0; k <= R; ++k) a[v][k] = reinterpret_cast<const u32x4*>(g.apack)[k * 64 + la];
+#pragma unroll
+      for (int k = 0; k < (R + 1) / 2; ++k) i[v][k] = g.ipack[k * 64 + la];
+    }
+  }
+};
+
+// The operand of two line pairs.  Which half holds which pair decides the order an
+// instruction sums them in, so it follows the pair's row in the grid, not its place
+// in the stream: the pair that starts at row y is in half floor(y / 2) % 2, and
+// results do not depend on segment heights or on how many steps a launch fuses.
+struct QuadB {
+  u32x4 p[2];
+};
+
+// acc += A_k x quad, newest pair in half NEW.
+// (NEW is a constant once the loops over levels unroll)
+template <int OP, int R, int K>
+__device__ __forceinline__ f32x4 quad_mma(int NEW, f32x4 acc, const QuadA<R>& A, const QuadB& b) {
+  return pair_mma<OP, 1, (K & 1)>(acc, A.a[1 - NEW][K], (u32x4){0, 0, 0, 0}, (u32x4){0, 0, 0, 0}, A.i[1 - NEW][K / 2],
+                                  b.p[0], b.p[1]);
+}
+
+// floor(y / 2) % 2 of the level-t pairs, less that of stream iteration P: they start
+// at row y0 - (T - t) R + 2 j, y0 a multiple of 4, j of P's parity.
+template <int R, int T>
+constexpr int quad_parity(int t) {
+  return (((T - t) * R + 1) / 2) & 1;
+}
+
+// Live output pairs of one level and half.  Pair j has arrived in half NEW of the
+// operand: quad (j - 1, j) completes output pair j - R and starts output pair
+// j - 1, which takes over its place (r = 1: they are the same, nothing is carried).
+template <int R>
+struct QuadAcc {
+  f32x4 s[R == 3 ? 2 : 1];
+  __device__ __forceinline__ void zero() { s[0] = s[R == 3 ? 1 : 0] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+};
+
+// T = 1 .. 4 steps per launch.  The stream of band2d_pair_tbt_body (kernels_band_pair.hip)
+// with quads: level t (0 = input, T = output) has its line pairs start at row y0 -
+// (T - t) r; at stream iteration P pass t multiplies the level-t pair P - t (r + 1),
+// staged (t = 0) or written to its two-slot LDS ring at P - 1.  A launch of one step
+// has no level between and stores the 256 columns it computes; T >= 2 steps store
+// pair_tb_width (240 at T = 2).
+constexpr int quad_width(int T, int R) {
+  return T == 1 ? kStripWPair : T == 2 ? kStripWPair2 : pair_tb_width(T, R);
+}
+constexpr int quad_margin(int T, int R) { return T <= 2 ? kPairWinLead : pair_tb_margin(T, R); }
+// LDS: two input line pairs and two pairs per level between.
+template <int T>
+constexpr int quad_lds_dw() {
+  return 4 * T * kPairRowDw;
+}
+
+// What a wave computes beyond the grid: nothing (0), columns (1), or rows and perhaps
+// columns (2); values there are the zero halo of the next step.
+template <int R, int T>
+__device__ __forceinline__ int quad_edge(const BandGrid& g, int w, bool aligned) {
+  if (T == 1) return 0;  // no step in between
+  const int strip = w % g.nstrips, seg = w / g.nstrips;
+  const int xp = strip * quad_width(T, R) - quad_margin(T, R);
+  const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
+  if ((y0 & ~3) - T * R < 0 || y0 + hrows + T * R + 2 > g.ny) return 2;
+  return xp >= 0 && xp + (aligned ? 256 : 260) <= g.nx ? 0 : 1;
+}
+
+template <int R, int OP, bool ALIGNED, int T, int EDGE>
+__device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint32_t* lds) {
+  constexpr int PAIR = 2 * kPairRowDw;
+  constexpr int MARGIN = quad_margin(T, R), WIDTH = quad_width(T, R);
+  const int lane = threadIdx.x;
+  const int strip = w % g.nstrips, seg = w / g.nstrips;
+  const int xp = strip * WIDTH - MARGIN;                // first computed column of every pass (4 mod 8)
+  const int x_lo = T == 1 ? 0 : strip * WIDTH;          // stored columns
+  // a segment that starts at row 2 mod 4 streams from the pair of rows before it
+  const int ys = seg * g.seg_h, y0 = ys & ~3;
+  const int hrows = min(g.seg_h, g.ny - ys) + (ys - y0);
+  const int npin = (hrows + 1) / 2 + T * R + (T - 1);  // input pairs streamed, in whole bodies of four
+  const int nit = (npin + 3) / 4 * 4;
+  const int nx = g.nx, ny = g.ny;
+  const int x_hi = T == 1 ? nx : min(nx, x_lo + WIDTH);
+
+  QuadA<R> A;
+  A.load(g, lane);
+  __builtin_amdgcn_s_waitcnt(0);
+
+  int p1, p2;
+  pair_gather_offsets(lane, &p1, &p2);
+  p1 += (lane >> 5) * kPairRowDw;  // lanes 32..63 feed the pair's second line
+  p2 += (lane >> 5) * kPairRowDw;
+  const bool stager = lane < kPairChunks;
+  const OddTail tail(ALIGNED ? 0 : nx, xp - kPairWinLead, 8 * kPairChunks);
+  const uint32_t lvoff =
+      tail.voff(stager ? (uint32_t)((xp - kPairWinLead + 8 * lane) * 2) : kOffNone, lane, nx);
+  const int lw = 6 * lane;
+  // this lane's 4 values of every pass: columns xo + e (half a) and xo + 128 + e (half b)
+  // of line 2m + (lane >> 5) of the pair
+  const int xo = xp + 8 * (lane & 15) + 4 * ((lane >> 4) & 1);
+  const int phi = lane >> 5;
+  const int line_off = phi * nx;
+  const PairStore<ALIGNED> ova(xo, line_off, x_lo, x_hi, nx, xp, 2), ovb(xo + 128, line_off, x_lo, x_hi, nx, xp + 128, 2);
+  // ragged widths: 16-bit lanes of the intermediate values inside the grid
+  uint32_t ma0 = 0, ma1 = 0, mb0 = 0, mb1 = 0;
+  if constexpr (!ALIGNED && T > 1) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t half = (e & 1) ? 0xffff0000u : 0x0000ffffu;
+      const int ya = xo + e, yb = xo + 128 + e;
+      if (ya >= 0 && ya < nx) (e < 2 ? ma0 : ma1) |= half;
+      if (yb >= 0 && yb < nx) (e < 2 ? mb0 : mb1) |= half;
+    }
+  }
+  // the input and the intermediate levels 1 .. T-1, each a ring of two LDS line pairs;
+  // this lane's 2 dwords of half a sit at data dword 4n + 2 + 2 (h & 1) of line phi,
+  // half b 96 further.  Quads outside the grid's columns go to the pad dwords behind
+  // their chunk instead (their own place keeps the zeros it starts with), so the waves
+  // at the grid's sides do no more than the others: masking their values took 20 %
+  // longer, and a launch lasts as long as its slowest wave.
+  const int odd_chunk = (lane >> 4) & 1;
+  const int mw = 6 * (lane & 15) + (odd_chunk ? 6 : 2) + phi * kPairRowDw;
+  int mwa = mw, mwb = mw + kPairHalfDw;
+  if constexpr (EDGE != 0) {
+    const int pad = odd_chunk ? 4 : 2;
+    if (xo + 4 <= 0 || xo >= nx) mwa += pad;
+    if (xo + 132 <= 0 || xo + 128 >= nx) mwb += pad;
+  }
+  for (int i = lane; i < (T - 1) * 2 * PAIR; i += 64) lds[2 * PAIR + i] = 0u;
+
+  LineWalk lin(g.in, y0 - T * R, max(0, y0 - T * R), min(ny, y0 + hrows + T * R), nx * 2);
+  // output pair P - (T - 1)(R + 1) - R is finished at iteration P
+  PairWalk pout(g.out, y0 - 2 * ((T - 1) * (R + 1) + R), ys, y0 + hrows, nx * 2);
+  // input pairs P + 2 and P + 3 are in registers or on their way while pair P is multiplied
+  u32x4 stg[2][2];
+  auto load = [&](u32x4* v) {
+    v[0] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
+    v[1] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
+  };
+  auto stage = [&](uint32_t* d, const u32x4* v) {
+    if (stager) {
+      store_chunk_lds(d, lw, v[0]);
+      store_chunk_lds(d + kPairRowDw, lw, v[1]);
+    }
+    if constexpr (!ALIGNED) {
+      tail.put(d, pair_dword(tail.at), lane, v[0]);
+      tail.put(d + kPairRowDw, pair_dword(tail.at), lane, v[1]);
+    }
+  };
+  load(stg[0]);
+  load(stg[1]);
+  stage(lds, stg[0]);
+  load(stg[0]);
+  QuadAcc<R> acc_a[T], acc_b[T];
+  QuadB ba[T], bb[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    acc_a[t].zero();
+    acc_b[t].zero();
+    ba[t].p[0] = ba[t].p[1] = bb[t].p[0] = bb[t].p[1] = (u32x4){0u, 0u, 0u, 0u};
+  }
+
+  auto iter = [&](int P, auto nc) {
+    constexpr int NEW = decltype(nc)::value;  // P % 2
+    wave_lds_sync();  // the pairs written last iteration are visible
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      // pass t reads the staged input pair P (t = 0) or the level-t pair written at P - 1
+      const uint32_t* l0 = lds + (t == 0 ? NEW : 2 * t + (1 - NEW)) * PAIR;
+      ba[t].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(l0, p1, p2);
+      bb[t].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(l0 + kPairHalfDw, p1, p2);
+    }
+    wave_lds_sync();
+    stage(lds + (1 - NEW) * PAIR, stg[1 - NEW]);  // input pair P + 1
+    load(stg[1 - NEW]);                            // input pair P + 3
+    // the chains of the levels and halves are independent: one instruction of each in turn
+    uint2 fa[T], fb[T];
+    if constexpr (R == 1) {
+      f32x4 sa[T], sb[T];
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        sa[t] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, ba[t]);
+        sb[t] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bb[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        sa[t] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), sa[t], A, ba[t]);
+        sb[t] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), sb[t], A, bb[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        fa[t] = pack_out<OP>(sa[t]);
+        fb[t] = pack_out<OP>(sb[t]);
+      }
+    } else {
+      constexpr int S = 1 - NEW;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        acc_a[t].s[S] = quad_mma<OP, R, 2>(NEW ^ quad_parity<R, T>(t), acc_a[t].s[S], A, ba[t]);
+        acc_b[t].s[S] = quad_mma<OP, R, 2>(NEW ^ quad_parity<R, T>(t), acc_b[t].s[S], A, bb[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        acc_a[t].s[S] = quad_mma<OP, R, 3>(NEW ^ quad_parity<R, T>(t), acc_a[t].s[S], A, ba[t]);
+        acc_b[t].s[S] = quad_mma<OP, R, 3>(NEW ^ quad_parity<R, T>(t), acc_b[t].s[S], A, bb[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        fa[t] = pack_out<OP>(acc_a[t].s[S]);
+        acc_a[t].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, ba[t]);
+        fb[t] = pack_out<OP>(acc_b[t].s[S]);
+        acc_b[t].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bb[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        acc_a[t].s[S] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), acc_a[t].s[S], A, ba[t]);
+        acc_b[t].s[S] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), acc_b[t].s[S], A, bb[t]);
+      }
+      // that order: a pair's conversion and the clearing of its place in the shadow of
+      // the matrix instruction before
+      __builtin_amdgcn_sched_group_barrier(0x008, 4 * T, 0);
+#pragma unroll
+      for (int i = 0; i < 2 * T; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 2 * T, 0);
+    }
+    // level-(t + 1) pair P - t (R + 1) - R is complete: round, zero outside the grid,
+    // keep it for pass t + 1 at the next iteration
+#pragma unroll
+    for (int t = 0; t + 1 < T; ++t) {
+      const int mrow0 = y0 - (T - 1 - t) * R + 2 * (P - t * (R + 1) - R);  // the phi = 0 row
+      const uint2 va = fa[t], vb = fb[t];
+      uint32_t* mc = lds + (2 * (t + 1) + NEW) * PAIR;
+      if constexpr (EDGE == 0) {
+        *reinterpret_cast<uint2*>(mc + mw) = va;
+        *reinterpret_cast<uint2*>(mc + mw + kPairHalfDw) = vb;
+      } else {
+        uint2 oa = va, ob = vb;
+        if constexpr (!ALIGNED) {
+          oa = make_uint2(va.x & ma0, va.y & ma1);
+          ob = make_uint2(vb.x & mb0, vb.y & mb1);
+        }
+        if constexpr (EDGE == 2) {
+          // (a branch over the few pairs that need it would cut the loop body in pieces, at
+          // the price of copies of the sums)
+          const uint32_t m = (unsigned)(mrow0 + phi) < (unsigned)ny ? 0xffffffffu : 0u;
+          oa = make_uint2(oa.x & m, oa.y & m);
+          ob = make_uint2(ob.x & m, ob.y & m);
+        }
+        *reinterpret_cast<uint2*>(mc + mwa) = oa;
+        *reinterpret_cast<uint2*>(mc + mwb) = ob;
+      }
+    }
+    const __amdgpu_buffer_rsrc_t rs = pout.next();
+    store_pair<ALIGNED>(rs, ova, fa[T - 1]);
+    store_pair<ALIGNED>(rs, ovb, fb[T - 1]);
+  };
+  for (int P = 0; P < nit; P += 2) {
+    iter(P, std::integral_constant<int, 0>{});
+    iter(P + 1, std::integral_constant<int, 1>{});
+  }
+}
+
+// The body of a paired-band step (T = 1) or of T fused ones for radius R.
+template <int R, int ENG>
+constexpr bool use_quad() {
+  return ENG == 1 && R != 2;
 }
 
 }  // namespace spider_impl

@@ -1221,6 +1221,28 @@ int band2d_blocks_per_cu(int r, int operand, int engine, bool aligned) {
 
 // ----------------------------------------------------------------------------- batched
 
+// A paired-band unit: one step, or two fused ones.
+template <int R, int OP, int ENG>
+__device__ __forceinline__ void batch_pair(const BandGrid& g, int w, uint32_t* lds, bool al, bool two) {
+  if constexpr (use_quad<R, ENG>()) {
+    if (two) {
+      if (al) band2d_quad_body<R, OP, true, 2, 2>(g, w, lds);
+      else band2d_quad_body<R, OP, false, 2, 2>(g, w, lds);
+    } else {
+      if (al) band2d_quad_body<R, OP, true, 1, 0>(g, w, lds);
+      else band2d_quad_body<R, OP, false, 1, 2>(g, w, lds);
+    }
+  } else {
+    if (two) {
+      if (al) band2d_pair_tb2_body<R, OP, ENG, true, true>(g, w, lds);
+      else band2d_pair_tb2_body<R, OP, ENG, false, true>(g, w, lds);
+    } else {
+      if (al) band2d_pair_body<R, OP, ENG, true>(g, w, lds);
+      else band2d_pair_body<R, OP, ENG, false>(g, w, lds);
+    }
+  }
+}
+
 // One workgroup per work unit (a strip segment of one grid); the launch has
 // exactly begin[n] workgroups.  CLS selects the bodies compiled in: 1 = 2-D
 // kinds, 2 = 3-D kinds, 3 = all.
@@ -1259,27 +1281,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(((CLS == 5 |
       case kB2dR1: if (al) band2d_body<1, OP, ENG, true>(g, w, lds); else band2d_body<1, OP, ENG, false>(g, w, lds); break;
       case kB2dR2: if (al) band2d_body<2, OP, ENG, true>(g, w, lds); else band2d_body<2, OP, ENG, false>(g, w, lds); break;
       case kB2dR3: if (al) band2d_body<3, OP, ENG, true>(g, w, lds); else band2d_body<3, OP, ENG, false>(g, w, lds); break;
-      case kB2dPairR1:
-        if (al) band2d_pair_body<1, OP, ENG, true>(g, w, lds); else band2d_pair_body<1, OP, ENG, false>(g, w, lds);
-        break;
-      case kB2dPairR2:
-        if (al) band2d_pair_body<2, OP, ENG, true>(g, w, lds); else band2d_pair_body<2, OP, ENG, false>(g, w, lds);
-        break;
-      case kB2dPairR3:
-        if (al) band2d_pair_body<3, OP, ENG, true>(g, w, lds); else band2d_pair_body<3, OP, ENG, false>(g, w, lds);
-        break;
-      case kB2dPairTb2R1:
-        if (al) band2d_pair_tb2_body<1, OP, ENG, true, true>(g, w, lds);
-        else band2d_pair_tb2_body<1, OP, ENG, false, true>(g, w, lds);
-        break;
-      case kB2dPairTb2R2:
-        if (al) band2d_pair_tb2_body<2, OP, ENG, true, true>(g, w, lds);
-        else band2d_pair_tb2_body<2, OP, ENG, false, true>(g, w, lds);
-        break;
-      case kB2dPairTb2R3:
-        if (al) band2d_pair_tb2_body<3, OP, ENG, true, true>(g, w, lds);
-        else band2d_pair_tb2_body<3, OP, ENG, false, true>(g, w, lds);
-        break;
+      case kB2dPairR1: batch_pair<1, OP, ENG>(g, w, lds, al, false); break;
+      case kB2dPairR2: batch_pair<2, OP, ENG>(g, w, lds, al, false); break;
+      case kB2dPairR3: batch_pair<3, OP, ENG>(g, w, lds, al, false); break;
+      case kB2dPairTb2R1: batch_pair<1, OP, ENG>(g, w, lds, al, true); break;
+      case kB2dPairTb2R2: batch_pair<2, OP, ENG>(g, w, lds, al, true); break;
+      case kB2dPairTb2R3: batch_pair<3, OP, ENG>(g, w, lds, al, true); break;
       default:
         break;
     }

@@ -24,18 +24,40 @@
 
 namespace spider_impl {
 
+// The quad body for what wave w computes beyond the grid.
+template <int R, int OP, bool ALIGNED, int T>
+__device__ __forceinline__ void quad_bodies(const BandGrid& g, int w, uint32_t* lds) {
+  const int edge = quad_edge<R, T>(g, w, true);
+  if (!ALIGNED && !pair_inside(g, w, quad_width(T, R), quad_margin(T, R)))
+    band2d_quad_body<R, OP, ALIGNED, T, 2>(g, w, lds);
+  else if (edge == 0)
+    band2d_quad_body<R, OP, true, T, 0>(g, w, lds);
+  else if (edge == 1)
+    band2d_quad_body<R, OP, true, T, 1>(g, w, lds);
+  else
+    band2d_quad_body<R, OP, true, T, 2>(g, w, lds);
+}
+
 // ALIGNED = false: widths that are not a multiple of 8; only the waves that stage the
 // end of the lines run the ragged bodies.
 template <int R, int OP, int ENG, bool ALIGNED>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ALIGNED ? 4 : (ENG == 1 ? 3 : 2)))) void band2d_pair_kernel(BandGrid g) {
   constexpr int NP = R + 1;
   constexpr int UP = (NP >= 3) ? NP : 2 * NP;
-  __shared__ uint32_t lds[2 * UP * kPairRowDw];
+  __shared__ uint32_t lds[use_quad<R, ENG>() ? quad_lds_dw<1>() : 2 * UP * kPairRowDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  if (ALIGNED || pair_inside(g, w, kStripWPair, kPairWinLead))
-    band2d_pair_body<R, OP, ENG, true>(g, w, lds);
-  else
-    band2d_pair_body<R, OP, ENG, ALIGNED>(g, w, lds);
+  const bool inside = ALIGNED || pair_inside(g, w, kStripWPair, kPairWinLead);
+  if constexpr (use_quad<R, ENG>()) {
+    if (inside)
+      band2d_quad_body<R, OP, true, 1, 0>(g, w, lds);
+    else
+      band2d_quad_body<R, OP, ALIGNED, 1, 2>(g, w, lds);
+  } else {
+    if (inside)
+      band2d_pair_body<R, OP, ENG, true>(g, w, lds);
+    else
+      band2d_pair_body<R, OP, ENG, ALIGNED>(g, w, lds);
+  }
 }
 
 // ----------------------------------------------------------------------------- two fused steps
@@ -45,19 +67,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ENG == 1 ? 3
     BandGrid g) {
   constexpr int NP = R + 1;
   constexpr int UP = (NP >= 3) ? NP : 2 * NP;
-  __shared__ uint32_t lds[(2 * UP + 4) * kPairRowDw];
+  __shared__ uint32_t lds[use_quad<R, ENG>() ? quad_lds_dw<2>() : (2 * UP + 4) * kPairRowDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
+  if constexpr (use_quad<R, ENG>()) {
+    quad_bodies<R, OP, ALIGNED, 2>(g, w, lds);
+    return;
+  }
   if constexpr (ENG == 1) {  // (a second body would spill the dense variants)
     // interior waves: columns [xp, xp + 256) and rows [y0 - 2R, y0 + hrows + 2R + 2) inside the grid
     const int strip = w % g.nstrips, seg = w / g.nstrips;
     const int xp = strip * kStripWPair2 - kPairWinLead;
     const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
     if (xp >= 0 && xp + (ALIGNED ? 256 : 260) <= g.nx && y0 - 2 * R >= 0 && y0 + hrows + 2 * R + 2 <= g.ny) {
-      band2d_pair_tb2_body<R, OP, ENG, true, false>(g, w, lds);
+      if constexpr (!use_quad<R, ENG>()) band2d_pair_tb2_body<R, OP, ENG, true, false>(g, w, lds);
       return;
     }
   }
-  band2d_pair_tb2_body<R, OP, ENG, ALIGNED, true>(g, w, lds);
+  if constexpr (!use_quad<R, ENG>()) band2d_pair_tb2_body<R, OP, ENG, ALIGNED, true>(g, w, lds);
 }
 
 // ----------------------------------------------------------------------------- T fused steps
@@ -253,8 +279,12 @@ template <int R, int OP, int ENG, bool ALIGNED, int T>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void band2d_pair_tbt_kernel(BandGrid g) {
   constexpr int NP = R + 1;
   constexpr int UP = (NP >= 3) ? NP : 2 * NP;
-  __shared__ uint32_t lds[(2 * UP + 4 * (T - 1)) * kPairRowDw];
+  __shared__ uint32_t lds[use_quad<R, ENG>() ? quad_lds_dw<T>() : (2 * UP + 4 * (T - 1)) * kPairRowDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
+  if constexpr (use_quad<R, ENG>()) {
+    quad_bodies<R, OP, ALIGNED, T>(g, w, lds);
+    return;
+  }
   // interior waves (most of a large grid) skip the masking of intermediate values:
   // columns [xp, xp + 256) and rows [y0 - T R, y0 + hrows + T R + 2) inside the grid
   const int strip = w % g.nstrips, seg = w / g.nstrips;
@@ -264,12 +294,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ba
   (void)interior;
   if constexpr (ENG == 1) {
     if (interior) {
-      band2d_pair_tbt_body<R, OP, ENG, true, T, false>(g, w, lds);
+      if constexpr (!use_quad<R, ENG>()) band2d_pair_tbt_body<R, OP, ENG, true, T, false>(g, w, lds);
       return;
     }
   }
   // (the dense engine keeps one body: its second copy would spill)
-  band2d_pair_tbt_body<R, OP, ENG, ALIGNED, T, true>(g, w, lds);
+  if constexpr (!use_quad<R, ENG>()) band2d_pair_tbt_body<R, OP, ENG, ALIGNED, T, true>(g, w, lds);
 }
 
 namespace {

@@ -18,6 +18,7 @@
 // result rounded to 16 bits equals the 16-bit carry's, bit for bit.
 #include <hip/hip_runtime.h>
 
+#include "band_f32_common.h"
 #include "band_pair.h"
 
 namespace spider_impl {
@@ -39,19 +40,6 @@ __device__ __forceinline__ PairF32Line load_pair_f32(__amdgpu_buffer_rsrc_t rs, 
   return L;
 }
 
-// Two fp32 values -> packed 16-bit hi = rnd(x) and lo = rnd(x - hi).
-template <int OP, bool XLO>
-__device__ __forceinline__ void split_pair(uint32_t a, uint32_t b, uint32_t* hi, uint32_t* lo) {
-  const float fa = __builtin_bit_cast(float, a), fb = __builtin_bit_cast(float, b);
-  *hi = pack2<OP>(fa, fb);
-  if constexpr (XLO) {
-    const f32x2 h = unpack2<OP>(*hi);
-    *lo = pack2<OP>(fa - h.x, fb - h.y);
-  } else {
-    *lo = 0u;
-  }
-}
-
 // Write a staged fp32 line as its hi (and lo) 16-bit LDS lines.
 //   mw: this lane's dword offset for its 4 values (data dwords 2l, 2l + 1)
 //   tw: byte offset of lane l < 8's extra value (data half 256 + l)
@@ -59,13 +47,13 @@ template <int OP, bool XLO>
 __device__ __forceinline__ void stage_pair_f32(uint32_t* hi, uint32_t* lo, int lane, int mw, int tw,
                                                const PairF32Line& L) {
   uint32_t h0, l0, h1, l1;
-  split_pair<OP, XLO>(L.m.x, L.m.y, &h0, &l0);
-  split_pair<OP, XLO>(L.m.z, L.m.w, &h1, &l1);
+  split2<OP, XLO>(L.m.x, L.m.y, &h0, &l0);
+  split2<OP, XLO>(L.m.z, L.m.w, &h1, &l1);
   *reinterpret_cast<uint2*>(hi + mw) = make_uint2(h0, h1);
   if constexpr (XLO) *reinterpret_cast<uint2*>(lo + mw) = make_uint2(l0, l1);
   if (lane < 8) {
     uint32_t th, tl;
-    split_pair<OP, XLO>(L.t, 0u, &th, &tl);
+    split2<OP, XLO>(L.t, 0u, &th, &tl);
     *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(hi) + tw) = (uint16_t)th;
     if constexpr (XLO) *reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(lo) + tw) = (uint16_t)tl;
   }
@@ -255,10 +243,10 @@ __device__ __forceinline__ void band2d_pair_f32_body12(const BandGrid& g, int w,
         const uint32_t rmask = (mrow >= 0 && mrow < ny) ? 0xffffffffu : 0u;
         const u32x4 va = __builtin_bit_cast(u32x4, a1[fs]), vb = __builtin_bit_cast(u32x4, b1[fs]);
         uint32_t ha0, la0, ha1, la1, hb0, lb0, hb1, lb1;
-        split_pair<OP, XLO>(va.x & ma[0] & rmask, va.y & ma[1] & rmask, &ha0, &la0);
-        split_pair<OP, XLO>(va.z & ma[2] & rmask, va.w & ma[3] & rmask, &ha1, &la1);
-        split_pair<OP, XLO>(vb.x & mb[0] & rmask, vb.y & mb[1] & rmask, &hb0, &lb0);
-        split_pair<OP, XLO>(vb.z & mb[2] & rmask, vb.w & mb[3] & rmask, &hb1, &lb1);
+        split2<OP, XLO>(va.x & ma[0] & rmask, va.y & ma[1] & rmask, &ha0, &la0);
+        split2<OP, XLO>(va.z & ma[2] & rmask, va.w & ma[3] & rmask, &ha1, &la1);
+        split2<OP, XLO>(vb.x & mb[0] & rmask, vb.y & mb[1] & rmask, &hb0, &lb0);
+        split2<OP, XLO>(vb.z & mb[2] & rmask, vb.w & mb[3] & rmask, &hb1, &lb1);
         uint32_t* mc = mid + (P & 1) * PAIRSZ;
         *reinterpret_cast<uint2*>(mc + mwo) = make_uint2(ha0, ha1);
         *reinterpret_cast<uint2*>(mc + mwo + kPairHalfDw) = make_uint2(hb0, hb1);
@@ -412,10 +400,10 @@ __device__ __forceinline__ void band2d_pair_f32_bodyT(const BandGrid& g, int w, 
           }
         }
         uint32_t ha0, la0, ha1, la1, hb0, lb0, hb1, lb1;
-        split_pair<OP, XLO>(va.x, va.y, &ha0, &la0);
-        split_pair<OP, XLO>(va.z, va.w, &ha1, &la1);
-        split_pair<OP, XLO>(vb.x, vb.y, &hb0, &lb0);
-        split_pair<OP, XLO>(vb.z, vb.w, &hb1, &lb1);
+        split2<OP, XLO>(va.x, va.y, &ha0, &la0);
+        split2<OP, XLO>(va.z, va.w, &ha1, &la1);
+        split2<OP, XLO>(vb.x, vb.y, &hb0, &lb0);
+        split2<OP, XLO>(vb.z, vb.w, &hb1, &lb1);
         uint32_t* mc = mid + (t * 2 + (P & 1)) * PAIRSZ;
         *reinterpret_cast<uint2*>(mc + mwo) = make_uint2(ha0, ha1);
         *reinterpret_cast<uint2*>(mc + mwo + kPairHalfDw) = make_uint2(hb0, hb1);
@@ -430,25 +418,211 @@ __device__ __forceinline__ void band2d_pair_f32_bodyT(const BandGrid& g, int w, 
 }
 #undef SPIDER_PAIR_PASS
 
+// Odd radii on the sparse engine: the stream of band2d_quad_body (band_pair.h) with
+// every line as a hi (and, XLO, a lo) 16-bit line and every instruction on the hi
+// and then on the lo quads.  Sums of a level leave as hi / lo lines of the next.
+template <int R, int OP, bool ALIGNED, bool XLO, int T, int EDGE>
+__device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, uint32_t* lds) {
+  constexpr int NS = XLO ? 2 : 1;
+  constexpr int LINE = kPairRowDw;
+  constexpr int PAIR = 2 * NS * LINE;  // hi lines at 0 / LINE, lo lines at 2 LINE / 3 LINE
+  constexpr int MARGIN = quad_margin(T, R), WIDTH = quad_width(T, R);
+  const int lane = threadIdx.x;
+  const int strip = w % g.nstrips, seg = w / g.nstrips;
+  const int xp = strip * WIDTH - MARGIN;
+  const int x_lo = T == 1 ? 0 : strip * WIDTH;
+  // a segment that starts at row 2 mod 4 streams from the pair of rows before it
+  const int ys = seg * g.seg_h, y0 = ys & ~3;
+  const int hrows = min(g.seg_h, g.ny - ys) + (ys - y0);
+  const int npin = (hrows + 1) / 2 + T * R + (T - 1);
+  const int nit = (npin + 3) / 4 * 4;
+  const int nx = g.nx, ny = g.ny;
+  const int x_hi = T == 1 ? nx : min(nx, x_lo + WIDTH);
+
+  QuadA<R> A;
+  A.load(g, lane);
+  __builtin_amdgcn_s_waitcnt(0);
+
+  int p1, p2;
+  pair_gather_offsets(lane, &p1, &p2);
+  p1 += (lane >> 5) * LINE;
+  p2 += (lane >> 5) * LINE;
+  // loads (byte offsets in an fp32 line): 4 values at xp - 4 + 4 lane, lanes < 8 one more at xp + 252 + lane
+  const uint32_t mvoff = (uint32_t)((xp - kPairWinLead + 4 * lane) * 4);
+  const uint32_t tvoff = lane < 8 ? (uint32_t)((xp + 252 + lane) * 4) : kOffNone;
+  const int mw = 6 * (lane >> 1) + 2 * (lane & 1);             // data dwords 2 lane, 2 lane + 1
+  const int tw = (6 * 32 + (lane >> 1)) * 4 + 2 * (lane & 1);  // data half 256 + lane (lane < 8)
+  // stores: lane (n, h) holds x = xp + 128 half + 8n + 4 (h & 1) + e of line 2m + (lane >> 5)
+  const int xo = xp + 8 * (lane & 15) + 4 * ((lane >> 4) & 1);
+  const int phi = lane >> 5;
+  const int line_off = phi * nx;
+  const PairStore<ALIGNED> ova(xo, line_off, x_lo, x_hi, nx, xp, 4), ovb(xo + 128, line_off, x_lo, x_hi, nx, xp + 128, 4);
+  // quads outside the grid's columns go to pad dwords (see band2d_quad_body)
+  const int odd_chunk = (lane >> 4) & 1;
+  const int mwo = 6 * (lane & 15) + (odd_chunk ? 6 : 2) + phi * LINE;
+  int mwf[2] = {mwo, mwo + kPairHalfDw};
+  if constexpr (EDGE != 0) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+      if (xo + 128 * f + 4 <= 0 || xo + 128 * f >= nx) mwf[f] += odd_chunk ? 4 : 2;
+  }
+  for (int i = lane; i < (T - 1) * 2 * PAIR; i += 64) lds[2 * PAIR + i] = 0u;
+
+  LineWalk lin(g.in, y0 - T * R, max(0, y0 - T * R), min(ny, y0 + hrows + T * R), nx * 4);
+  PairWalk pout(g.out, y0 - 2 * ((T - 1) * (R + 1) + R), ys, y0 + hrows, nx * 4);
+  PairF32Line stg[2][2];
+  auto load = [&](PairF32Line* v) {
+    v[0] = load_pair_f32(lin.next(), mvoff, tvoff);
+    v[1] = load_pair_f32(lin.next(), mvoff, tvoff);
+  };
+  auto stage = [&](uint32_t* d, const PairF32Line* v) {
+    stage_pair_f32<OP, XLO>(d, d + 2 * LINE, lane, mw, tw, v[0]);
+    stage_pair_f32<OP, XLO>(d + LINE, d + 3 * LINE, lane, mw, tw, v[1]);
+  };
+  load(stg[0]);
+  load(stg[1]);
+  stage(lds, stg[0]);
+  load(stg[0]);
+  QuadAcc<R> acc[T][2];
+  QuadB bq[T][2][NS];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      acc[t][f].zero();
+#pragma unroll
+      for (int s = 0; s < NS; ++s) bq[t][f][s].p[0] = bq[t][f][s].p[1] = (u32x4){0u, 0u, 0u, 0u};
+    }
+
+  auto iter = [&](int P, auto nc) {
+    constexpr int NEW = decltype(nc)::value;  // P % 2
+    wave_lds_sync();  // the pairs written last iteration are visible
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const uint32_t* l0 = lds + (t == 0 ? NEW : 2 * t + (1 - NEW)) * PAIR;
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+          bq[t][f][s].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(l0 + f * kPairHalfDw + s * 2 * LINE, p1, p2);
+    }
+    wave_lds_sync();
+    stage(lds + (1 - NEW) * PAIR, stg[1 - NEW]);  // input pair P + 1
+    load(stg[1 - NEW]);                            // input pair P + 3
+    // level t's finished pair: the output, or zeroed outside the grid and split for
+    // the next level
+    const __amdgpu_buffer_rsrc_t rs = pout.next();
+    auto emit = [&](int t, int f, f32x4 v) {
+      if (t == T - 1) {
+        store_pair_f32<ALIGNED>(rs, f ? ovb : ova, v);
+        return;
+      }
+      u32x4 u = __builtin_bit_cast(u32x4, v);
+      if constexpr (!ALIGNED) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = (unsigned)(xo + 128 * f + e) < (unsigned)nx ? u[e] : 0u;
+      }
+      if constexpr (EDGE == 2) {
+        const int mrow0 = y0 - (T - 1 - t) * R + 2 * (P - t * (R + 1) - R);
+        const uint32_t m = (unsigned)(mrow0 + phi) < (unsigned)ny ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] &= m;
+      }
+      uint32_t h0, l0, h1, l1;
+      split2<OP, XLO>(u.x, u.y, &h0, &l0);
+      split2<OP, XLO>(u.z, u.w, &h1, &l1);
+      uint32_t* mc = lds + (2 * (t + 1) + NEW) * PAIR + (EDGE != 0 ? mwf[f] : mwo + f * kPairHalfDw);
+      *reinterpret_cast<uint2*>(mc) = make_uint2(h0, h1);
+      if constexpr (XLO) *reinterpret_cast<uint2*>(mc + 2 * LINE) = make_uint2(l0, l1);
+    };
+    if constexpr (R == 1) {
+      f32x4 sum[T][2];
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) sum[t][f] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bq[t][f][0]);
+      if constexpr (XLO) {
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+          for (int f = 0; f < 2; ++f) sum[t][f] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), sum[t][f], A, bq[t][f][NS - 1]);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) sum[t][f] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), sum[t][f], A, bq[t][f][0]);
+      if constexpr (XLO) {
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+          for (int f = 0; f < 2; ++f) sum[t][f] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), sum[t][f], A, bq[t][f][NS - 1]);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) emit(t, f, sum[t][f]);
+    } else {
+      constexpr int S = 1 - NEW;
+      auto each = [&](auto kc, int s) {
+        constexpr int K = decltype(kc)::value;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+          for (int f = 0; f < 2; ++f) acc[t][f].s[S] = quad_mma<OP, R, K>(NEW ^ quad_parity<R, T>(t), acc[t][f].s[S], A, bq[t][f][s]);
+      };
+      each(std::integral_constant<int, 2>{}, 0);
+      if constexpr (XLO) each(std::integral_constant<int, 2>{}, NS - 1);
+      each(std::integral_constant<int, 3>{}, 0);
+      if constexpr (XLO) each(std::integral_constant<int, 3>{}, NS - 1);
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+          emit(t, f, acc[t][f].s[S]);
+          acc[t][f].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bq[t][f][0]);
+        }
+      if constexpr (XLO) each(std::integral_constant<int, 0>{}, NS - 1);
+      each(std::integral_constant<int, 1>{}, 0);
+      if constexpr (XLO) each(std::integral_constant<int, 1>{}, NS - 1);
+    }
+  };
+  for (int P = 0; P < nit; P += 2) {
+    iter(P, std::integral_constant<int, 0>{});
+    iter(P + 1, std::integral_constant<int, 1>{});
+  }
+}
+
 template <int R, int OP, int ENG, bool ALIGNED, bool XLO, int T>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((ENG == 1 && T == 1) ? (ALIGNED ? 4 : 3) : 2)))
 void band2d_pair_f32_kernel(BandGrid g) {
   constexpr int PAIRSZ = 2 * (XLO ? 2 : 1) * kPairRowDw;
   __shared__ uint32_t lds[2 * T * PAIRSZ];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  if constexpr (T <= 2) {
-    // (only the waves at the end of the lines need the ragged stores)
-    if (ALIGNED || pair_inside(g, w, T == 2 ? kStripWPair2 : kStripWPair, kPairWinLead))
+  // interior waves (every staged column and rows [y0 - T r, y0 + hrows + T r + 2) inside
+  // the grid) skip the zeroing of intermediate values outside it; only the waves at
+  // the end of the lines need the ragged stores
+  const int strip = w % g.nstrips, seg = w / g.nstrips;
+  const int xp = strip * quad_width(T, R) - quad_margin(T, R);
+  const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
+  const bool inside_x = ALIGNED || xp + 260 <= g.nx;
+  const bool interior = xp >= 0 && xp + 256 <= g.nx && y0 - T * R >= 0 && y0 + hrows + T * R + 2 <= g.ny;
+  if constexpr (use_quad<R, ENG>()) {
+    const int edge = quad_edge<R, T>(g, w, true);
+    if (!inside_x)
+      band2d_quad_f32_body<R, OP, ALIGNED, XLO, T, 2>(g, w, lds);
+    else if (edge == 0)
+      band2d_quad_f32_body<R, OP, true, XLO, T, 0>(g, w, lds);
+    else if (edge == 1)
+      band2d_quad_f32_body<R, OP, true, XLO, T, T == 1 ? 0 : 1>(g, w, lds);
+    else
+      band2d_quad_f32_body<R, OP, true, XLO, T, T == 1 ? 0 : 2>(g, w, lds);
+  } else if constexpr (T <= 2) {
+    if (inside_x)
       band2d_pair_f32_body12<R, OP, ENG, true, XLO, T == 2>(g, w, lds);
     else
       band2d_pair_f32_body12<R, OP, ENG, ALIGNED, XLO, T == 2>(g, w, lds);
   } else {
-    // interior waves (columns [xp, xp + 256) and rows [y0 - T r, y0 + hrows + T r + 2)
-    // inside the grid) skip the zeroing of intermediate values outside it
-    const int strip = w % g.nstrips, seg = w / g.nstrips;
-    const int xp = strip * pair_tb_width(T, R) - pair_tb_margin(T, R);
-    const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
-    if (xp >= 0 && xp + 256 <= g.nx && y0 - T * R >= 0 && y0 + hrows + T * R + 2 <= g.ny)
+    if (interior)
       band2d_pair_f32_bodyT<R, OP, ENG, true, XLO, T, false>(g, w, lds);
     else
       band2d_pair_f32_bodyT<R, OP, ENG, ALIGNED, XLO, T, true>(g, w, lds);

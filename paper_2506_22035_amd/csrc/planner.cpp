@@ -245,16 +245,10 @@ void pair_gather_positions(int pos[kPairWin]) {
   }
 }
 
-bool pack_pair(const double* w, int r, int operand, int split, int k, PackedRow* out, std::string* err) {
-  if (!w || !out || r < 1 || r > 3 || (operand != 2 && operand != 3) || (split != 1 && split != 2) || k < 0 ||
-      k > r) {
-    if (err) *err = "pack_pair: bad arguments (r in 1..3, operand f16/bf16, split 1/2, k in 0..r)";
-    return false;
-  }
-  const int kw = 2 * r + 1;
-  double hi[49], lo[49];
-  uint16_t hib[49], lob[49];
-  for (int t = 0; t < kw * kw; ++t) {
+// hi and lo parts (values and encodings) of n coefficients.
+static bool split_coeffs(const double* w, int n, int operand, int split, double* hi, double* lo, uint16_t* hib,
+                         uint16_t* lob, std::string* err) {
+  for (int t = 0; t < n; ++t) {
     hi[t] = operand == 2 ? round_f16(w[t], &hib[t]) : round_bf16(w[t], &hib[t]);
     if (!std::isfinite(hi[t])) {
       if (err) *err = "a coefficient lies beyond the range of the 16-bit operand type";
@@ -268,6 +262,42 @@ bool pack_pair(const double* w, int r, int operand, int split, int k, PackedRow*
       lob[t] = 0;
     }
   }
+  return true;
+}
+
+// Compress a 16 x 64 operand (values M, encodings B) into smfmac lanes.
+static bool pack_a64(const double (*M)[64], const uint16_t (*B)[64], PackedRow* out) {
+  double vals[16 * 32];
+  uint8_t meta[16 * 32];
+  if (!compress_24(&M[0][0], 16, 64, vals, meta)) return false;
+  std::memset(out, 0, sizeof(*out));
+  // smfmac A: lane la = m + 16 ga holds row m, K slots 16 ga .. 16 ga + 15 (four
+  // groups); element ea is value ea % 2 of group 4 ga + ea / 2, its 2-bit position
+  // at bits 2 ea of the index field.
+  for (int la = 0; la < 64; ++la) {
+    const int m = la % 16, ga = la / 16;
+    uint16_t field = 0;
+    for (int ea = 0; ea < 8; ++ea) {
+      const int G = 4 * ga + ea / 2;
+      const int p = meta[m * 32 + 2 * G + ea % 2];
+      out->a[la * 8 + ea] = B[m][4 * G + p];
+      field |= (uint16_t)(p << (2 * ea));
+    }
+    out->idx[la] = field;
+  }
+  return true;
+}
+
+bool pack_pair(const double* w, int r, int operand, int split, int k, PackedRow* out, std::string* err) {
+  if (!w || !out || r < 1 || r > 3 || (operand != 2 && operand != 3) || (split != 1 && split != 2) || k < 0 ||
+      k > r) {
+    if (err) *err = "pack_pair: bad arguments (r in 1..3, operand f16/bf16, split 1/2, k in 0..r)";
+    return false;
+  }
+  const int kw = 2 * r + 1;
+  double hi[49], lo[49];
+  uint16_t hib[49], lob[49];
+  if (!split_coeffs(w, kw * kw, operand, split, hi, lo, hib, lob, err)) return false;
   int pos[kPairWin];
   pair_gather_positions(pos);
   // Full 16 x 64 operand: row 8 phi + m, K slot 32 lambda + 16 rho + s.
@@ -289,26 +319,9 @@ bool pack_pair(const double* w, int r, int operand, int split, int k, PackedRow*
             M[8 * phi + m][32 * lam + 16 * rho + s] = v;
             B[8 * phi + m][32 * lam + 16 * rho + s] = v == 0.0 ? 0 : b;
           }
-  double vals[16 * 32];
-  uint8_t meta[16 * 32];
-  if (!compress_24(&M[0][0], 16, 64, vals, meta)) {
+  if (!pack_a64(M, B, out)) {
     if (err) *err = "pack_pair: band is not 2:4";
     return false;
-  }
-  std::memset(out, 0, sizeof(*out));
-  // smfmac A: lane la = m + 16 ga holds row m, K slots 16 ga .. 16 ga + 15 (four
-  // groups); element ea is value ea % 2 of group 4 ga + ea / 2, its 2-bit position
-  // at bits 2 ea of the index field.
-  for (int la = 0; la < 64; ++la) {
-    const int m = la % 16, ga = la / 16;
-    uint16_t field = 0;
-    for (int ea = 0; ea < 8; ++ea) {
-      const int G = 4 * ga + ea / 2;
-      const int p = meta[m * 32 + 2 * G + ea % 2];
-      out->a[la * 8 + ea] = B[m][4 * G + p];
-      field |= (uint16_t)(p << (2 * ea));
-    }
-    out->idx[la] = field;
   }
   // dense A: lane la: row la % 16, K slots 8 (la / 16) .. + 7 of each 32-slot half
   for (int la = 0; la < 64; ++la) {
@@ -317,6 +330,42 @@ bool pack_pair(const double* w, int r, int operand, int split, int k, PackedRow*
       out->dense[la * 16 + e] = B[m][8 * (la / 16) + e];
       out->dense[la * 16 + 8 + e] = B[m][32 + 8 * (la / 16) + e];
     }
+  }
+  return true;
+}
+
+bool pack_quad(const double* w, int r, int operand, int split, int k, PackedRow* out, std::string* err) {
+  if (!w || !out || (r != 1 && r != 3) || (operand != 2 && operand != 3) || (split != 1 && split != 2) || k < 0 ||
+      k > r) {
+    if (err) *err = "pack_quad: bad arguments (r 1 or 3, operand f16/bf16, split 1/2, k in 0..r)";
+    return false;
+  }
+  const int kw = 2 * r + 1, g = k / 2, part = k % 2;
+  double hi[49], lo[49];
+  uint16_t hib[49], lob[49];
+  if (!split_coeffs(w, kw * kw, operand, split, hi, lo, hib, lob, err)) return false;
+  int pos[kPairWin];
+  pair_gather_positions(pos);
+  double M[16][64];
+  uint16_t B[16][64];
+  for (int phi = 0; phi < 2; ++phi)
+    for (int m = 0; m < kPairM; ++m)
+      for (int line = 0; line < 4; ++line)
+        for (int s = 0; s < kPairWin; ++s) {
+          const int row = 4 * g + line - phi;        // kernel row (dy + r)
+          const int t = pos[s] - kPairLead - m + r;  // tap (dx + r)
+          double v = 0.0;
+          uint16_t b = 0;
+          if (row >= 0 && row < kw && t >= 0 && t < kw) {
+            v = part == 0 ? hi[row * kw + t] : lo[row * kw + t];
+            b = part == 0 ? hib[row * kw + t] : lob[row * kw + t];
+          }
+          M[8 * phi + m][16 * line + s] = v;
+          B[8 * phi + m][16 * line + s] = v == 0.0 ? 0 : b;
+        }
+  if (!pack_a64(M, B, out)) {
+    if (err) *err = "pack_quad: band is not 2:4";
+    return false;
   }
   return true;
 }

@@ -62,4 +62,14 @@ void pair_gather_positions(int pos[kPairWin]);
 // then 8 of K 32..63 (line j + 1), for two v_mfma_f32_16x16x32.
 bool pack_pair(const double* w, int r, int operand, int split, int k, PackedRow* out, std::string* err);
 
+// Odd radii on the sparse engine: the K = 64 slots hold four input lines, a pair
+// (j, j + 1) and the next (j + 2, j + 3), one copy of each line's window; the hi and
+// the lo part of the coefficients are instructions of their own.  Output pair (i,
+// i + 1) takes the input lines i - r .. i + r + 1, 2r + 2 of them: one quad of lines
+// at r = 1, two at r = 3, the first starting at line i - r.  Instruction k = 2 g + part
+// (0 .. r) is quad g's hi (part 0) or lo (part 1) coefficients: row 8 phi + m, K slot
+// 32 kappa + 16 lambda + s (line j + 2 kappa + lambda) holds kernel row 4 g + 2 kappa +
+// lambda - phi.  Only a and idx of `out` are set.
+bool pack_quad(const double* w, int r, int operand, int split, int k, PackedRow* out, std::string* err);
+
 }  // namespace spider_impl

@@ -765,7 +765,10 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
       for (int t = 0; t < kw && !pair; ++t) nz |= row[t] != 0.0;
       if (nz) mask |= 1u << i;
       std::string err;
-      const bool ok = pair ? pack_pair(p->coeffs.data(), radius, p->operand, std::min(p->split, 2), i, &rows[i], &err)
+      // (odd radii on the sparse engine: four input lines per instruction)
+      const bool quad = pair && radius != 2 && engine == SPIDER_ENGINE_SPARSE;
+      const bool ok = quad ? pack_quad(p->coeffs.data(), radius, p->operand, std::min(p->split, 2), i, &rows[i], &err)
+                    : pair ? pack_pair(p->coeffs.data(), radius, p->operand, std::min(p->split, 2), i, &rows[i], &err)
                            : pack_row(row, radius, p->operand, std::min(p->split, 2), &rows[i], &err);
       if (!ok) {
         spider_plan_destroy(p);
@@ -938,10 +941,12 @@ spider_status spider_plan_info(spider_plan_t p, int* engine, int* carry, int* ti
 // mfma), twice over for an fp32 carry split into three terms (hi and lo lines).
 static uint64_t pair_launch_instructions(const spider_plan_s* p, const BandGrid& g, int T) {
   const int np = p->r + 1, up = np >= 3 ? np : 2 * np;
+  const bool quad = p->r != 2 && p->engine == SPIDER_ENGINE_SPARSE;
   uint64_t iters = 0;
   for (int s = 0; s < g.nsegs_y; ++s) {
     const int hrows = std::min(g.seg_h, g.ny - s * g.seg_h);
-    const int npin = (hrows + 1) / 2 + T * p->r + (T - 1);
+    int npin = (hrows + 1) / 2 + T * p->r + (T - 1);
+    if (quad && (s * g.seg_h) % 4) ++npin;  // streamed from the pair of rows before it
     iters += (uint64_t)((npin + up - 1) / up) * up;
   }
   const int nlp = (p->carry == SPIDER_F32 && p->split == 3) ? 2 : 1;
