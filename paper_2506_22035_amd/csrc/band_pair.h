@@ -490,17 +490,20 @@ struct QuadAcc {
 // T = 1 .. 4 steps per launch.  The stream of band2d_pair_tbt_body (kernels_band_pair.hip)
 // with quads: level t (0 = input, T = output) has its line pairs start at row y0 -
 // (T - t) r; at stream iteration P pass t multiplies the level-t pair P - t (r + 1),
-// staged (t = 0) or written to its two-slot LDS ring at P - 1.  A launch of one step
+// staged (t = 0) or written by pass t - 1 in iteration P - 1.  An iteration completes
+// its output pairs first, writes them, and only then starts the next ones (r = 3),
+// gathering the next iteration's lines between those instructions: the LDS round
+// trip is covered by matrix work, and one pair per level is all the LDS holds.  A launch of one step
 // has no level between and stores the 256 columns it computes; T >= 2 steps store
 // pair_tb_width (240 at T = 2).
 constexpr int quad_width(int T, int R) {
   return T == 1 ? kStripWPair : T == 2 ? kStripWPair2 : pair_tb_width(T, R);
 }
 constexpr int quad_margin(int T, int R) { return T <= 2 ? kPairWinLead : pair_tb_margin(T, R); }
-// LDS: two input line pairs and two pairs per level between.
+// LDS: one line pair of the input and of every level between.
 template <int T>
 constexpr int quad_lds_dw() {
-  return 4 * T * kPairRowDw;
+  return 2 * T * kPairRowDw;
 }
 
 // What a wave computes beyond the grid: nothing (0), columns (1), or rows and perhaps
@@ -561,8 +564,7 @@ __device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint3
       if (yb >= 0 && yb < nx) (e < 2 ? mb0 : mb1) |= half;
     }
   }
-  // the input and the intermediate levels 1 .. T-1, each a ring of two LDS line pairs;
-  // this lane's 2 dwords of half a sit at data dword 4n + 2 + 2 (h & 1) of line phi,
+  // the input and the intermediate levels 1 .. T-1, an LDS line pair each; this lane's 2 dwords of half a sit at data dword 4n + 2 + 2 (h & 1) of line phi,
   // half b 96 further.  Quads outside the grid's columns go to the pad dwords behind
   // their chunk instead (their own place keeps the zeros it starts with), so the waves
   // at the grid's sides do no more than the others: masking their values took 20 %
@@ -575,12 +577,12 @@ __device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint3
     if (xo + 4 <= 0 || xo >= nx) mwa += pad;
     if (xo + 132 <= 0 || xo + 128 >= nx) mwb += pad;
   }
-  for (int i = lane; i < (T - 1) * 2 * PAIR; i += 64) lds[2 * PAIR + i] = 0u;
+  for (int i = lane; i < (T - 1) * PAIR; i += 64) lds[PAIR + i] = 0u;
 
   LineWalk lin(g.in, y0 - T * R, max(0, y0 - T * R), min(ny, y0 + hrows + T * R), nx * 2);
   // output pair P - (T - 1)(R + 1) - R is finished at iteration P
   PairWalk pout(g.out, y0 - 2 * ((T - 1) * (R + 1) + R), ys, y0 + hrows, nx * 2);
-  // input pairs P + 2 and P + 3 are in registers or on their way while pair P is multiplied
+  // input pairs P + 1 and P + 2 are in registers or on their way when iteration P begins
   u32x4 stg[2][2];
   auto load = [&](u32x4* v) {
     v[0] = load_row_chunk<ALIGNED>(lin.next(), lvoff, nx);
@@ -609,20 +611,17 @@ __device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint3
     ba[t].p[0] = ba[t].p[1] = bb[t].p[0] = bb[t].p[1] = (u32x4){0u, 0u, 0u, 0u};
   }
 
-  auto iter = [&](int P, auto nc) {
-    constexpr int NEW = decltype(nc)::value;  // P % 2
-    wave_lds_sync();  // the pairs written last iteration are visible
+  // pass t's next line pair, into half NEW of its operands
+  auto gather = [&](int t, int NEW) {
+    ba[t].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(lds + t * PAIR, p1, p2);
+    bb[t].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(lds + t * PAIR + kPairHalfDw, p1, p2);
+  };
+  wave_lds_sync();
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      // pass t reads the staged input pair P (t = 0) or the level-t pair written at P - 1
-      const uint32_t* l0 = lds + (t == 0 ? NEW : 2 * t + (1 - NEW)) * PAIR;
-      ba[t].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(l0, p1, p2);
-      bb[t].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(l0 + kPairHalfDw, p1, p2);
-    }
-    wave_lds_sync();
-    stage(lds + (1 - NEW) * PAIR, stg[1 - NEW]);  // input pair P + 1
-    load(stg[1 - NEW]);                            // input pair P + 3
-    // the chains of the levels and halves are independent: one instruction of each in turn
+  for (int t = 0; t < T; ++t) gather(t, 0);
+
+  auto iter = [&](int P, auto nc) {
+    constexpr int NEW = decltype(nc)::value, S = 1 - NEW;  // P % 2; the place of the pairs completed now
     uint2 fa[T], fb[T];
     if constexpr (R == 1) {
       f32x4 sa[T], sb[T];
@@ -642,7 +641,7 @@ __device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint3
         fb[t] = pack_out<OP>(sb[t]);
       }
     } else {
-      constexpr int S = 1 - NEW;
+      // the chains of the levels and halves are independent: one instruction of each in turn
 #pragma unroll
       for (int t = 0; t < T; ++t) {
         acc_a[t].s[S] = quad_mma<OP, R, 2>(NEW ^ quad_parity<R, T>(t), acc_a[t].s[S], A, ba[t]);
@@ -656,55 +655,61 @@ __device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint3
 #pragma unroll
       for (int t = 0; t < T; ++t) {
         fa[t] = pack_out<OP>(acc_a[t].s[S]);
-        acc_a[t].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, ba[t]);
         fb[t] = pack_out<OP>(acc_b[t].s[S]);
-        acc_b[t].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bb[t]);
       }
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        acc_a[t].s[S] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), acc_a[t].s[S], A, ba[t]);
-        acc_b[t].s[S] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), acc_b[t].s[S], A, bb[t]);
-      }
-      // that order: a pair's conversion and the clearing of its place in the shadow of
-      // the matrix instruction before
-      __builtin_amdgcn_sched_group_barrier(0x008, 4 * T, 0);
-#pragma unroll
-      for (int i = 0; i < 2 * T; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2 * T, 0);
     }
     // level-(t + 1) pair P - t (R + 1) - R is complete: round, zero outside the grid,
     // keep it for pass t + 1 at the next iteration
 #pragma unroll
     for (int t = 0; t + 1 < T; ++t) {
       const int mrow0 = y0 - (T - 1 - t) * R + 2 * (P - t * (R + 1) - R);  // the phi = 0 row
-      const uint2 va = fa[t], vb = fb[t];
-      uint32_t* mc = lds + (2 * (t + 1) + NEW) * PAIR;
-      if constexpr (EDGE == 0) {
-        *reinterpret_cast<uint2*>(mc + mw) = va;
-        *reinterpret_cast<uint2*>(mc + mw + kPairHalfDw) = vb;
-      } else {
-        uint2 oa = va, ob = vb;
-        if constexpr (!ALIGNED) {
-          oa = make_uint2(va.x & ma0, va.y & ma1);
-          ob = make_uint2(vb.x & mb0, vb.y & mb1);
-        }
-        if constexpr (EDGE == 2) {
-          // (a branch over the few pairs that need it would cut the loop body in pieces, at
-          // the price of copies of the sums)
-          const uint32_t m = (unsigned)(mrow0 + phi) < (unsigned)ny ? 0xffffffffu : 0u;
-          oa = make_uint2(oa.x & m, oa.y & m);
-          ob = make_uint2(ob.x & m, ob.y & m);
-        }
-        *reinterpret_cast<uint2*>(mc + mwa) = oa;
-        *reinterpret_cast<uint2*>(mc + mwb) = ob;
+      uint32_t* mc = lds + (t + 1) * PAIR;
+      uint2 oa = fa[t], ob = fb[t];
+      if constexpr (!ALIGNED) {
+        oa = make_uint2(oa.x & ma0, oa.y & ma1);
+        ob = make_uint2(ob.x & mb0, ob.y & mb1);
       }
+      if constexpr (EDGE == 2) {
+        // (a branch over the few pairs that need it would cut the loop body in pieces, at
+        // the price of copies of the sums)
+        const uint32_t m = (unsigned)(mrow0 + phi) < (unsigned)ny ? 0xffffffffu : 0u;
+        oa = make_uint2(oa.x & m, oa.y & m);
+        ob = make_uint2(ob.x & m, ob.y & m);
+      }
+      *reinterpret_cast<uint2*>(mc + (EDGE == 0 ? mw : mwa)) = oa;
+      *reinterpret_cast<uint2*>(mc + (EDGE == 0 ? mw + kPairHalfDw : mwb)) = ob;
     }
+    stage(lds, stg[1 - NEW]);  // input pair P + 1
+    load(stg[1 - NEW]);        // input pair P + 3
     const __amdgpu_buffer_rsrc_t rs = pout.next();
     store_pair<ALIGNED>(rs, ova, fa[T - 1]);
     store_pair<ALIGNED>(rs, ovb, fb[T - 1]);
+    wave_lds_sync();  // the pairs written are visible
+    if constexpr (R == 3) {
+      // each level's lines of the next iteration replace the older pair of its operands as
+      // soon as its last instruction has been issued
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        acc_a[t].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, ba[t]);
+        acc_b[t].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bb[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        acc_a[t].s[S] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), acc_a[t].s[S], A, ba[t]);
+        acc_b[t].s[S] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), acc_b[t].s[S], A, bb[t]);
+        gather(t, 1 - NEW);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 2 * T, 0);
+#pragma unroll
+      for (int i = 0; i < 2 * T; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < T; ++t) gather(t, 1 - NEW);
+    }
+    wave_lds_sync();
   };
   for (int P = 0; P < nit; P += 2) {
     iter(P, std::integral_constant<int, 0>{});

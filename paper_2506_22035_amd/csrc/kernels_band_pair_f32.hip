@@ -466,7 +466,7 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
     for (int f = 0; f < 2; ++f)
       if (xo + 128 * f + 4 <= 0 || xo + 128 * f >= nx) mwf[f] += odd_chunk ? 4 : 2;
   }
-  for (int i = lane; i < (T - 1) * 2 * PAIR; i += 64) lds[2 * PAIR + i] = 0u;
+  for (int i = lane; i < (T - 1) * PAIR; i += 64) lds[PAIR + i] = 0u;
 
   LineWalk lin(g.in, y0 - T * R, max(0, y0 - T * R), min(ny, y0 + hrows + T * R), nx * 4);
   PairWalk pout(g.out, y0 - 2 * ((T - 1) * (R + 1) + R), ys, y0 + hrows, nx * 4);
@@ -494,21 +494,39 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
       for (int s = 0; s < NS; ++s) bq[t][f][s].p[0] = bq[t][f][s].p[1] = (u32x4){0u, 0u, 0u, 0u};
     }
 
+  // pass t's next line pair, into half NEW of its operands
+  auto gather = [&](int t, int f, int NEW) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      bq[t][f][s].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(lds + t * PAIR + f * kPairHalfDw + s * 2 * LINE, p1, p2);
+  };
+  wave_lds_sync();
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    gather(t, 0, 0);
+    gather(t, 1, 0);
+  }
+
   auto iter = [&](int P, auto nc) {
-    constexpr int NEW = decltype(nc)::value;  // P % 2
-    wave_lds_sync();  // the pairs written last iteration are visible
+    constexpr int NEW = decltype(nc)::value, S = R == 3 ? 1 - NEW : 0;  // P % 2; the place of the pairs completed now
+    auto each = [&](auto kc, int s) {
+      constexpr int K = decltype(kc)::value;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const uint32_t* l0 = lds + (t == 0 ? NEW : 2 * t + (1 - NEW)) * PAIR;
+      for (int t = 0; t < T; ++t)
 #pragma unroll
-      for (int f = 0; f < 2; ++f)
+        for (int f = 0; f < 2; ++f)
+          acc[t][f].s[S] = quad_mma<OP, R, K>(NEW ^ quad_parity<R, T>(t), acc[t][f].s[S], A, bq[t][f][s]);
+    };
+    // the instructions that complete a pair: the second quad's (r = 3), or all (r = 1)
+    constexpr int K0 = R == 3 ? 2 : 0;
+    if constexpr (R == 1) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s)
-          bq[t][f][s].p[NEW ^ quad_parity<R, T>(t)] = pair_gather(l0 + f * kPairHalfDw + s * 2 * LINE, p1, p2);
+      for (int t = 0; t < T; ++t) acc[t][0].s[0] = acc[t][1].s[0] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
-    wave_lds_sync();
-    stage(lds + (1 - NEW) * PAIR, stg[1 - NEW]);  // input pair P + 1
-    load(stg[1 - NEW]);                            // input pair P + 3
+    each(std::integral_constant<int, K0>{}, 0);
+    if constexpr (XLO) each(std::integral_constant<int, K0>{}, NS - 1);
+    each(std::integral_constant<int, K0 + 1>{}, 0);
+    if constexpr (XLO) each(std::integral_constant<int, K0 + 1>{}, NS - 1);
     // level t's finished pair: the output, or zeroed outside the grid and split for
     // the next level
     const __amdgpu_buffer_rsrc_t rs = pout.next();
@@ -531,60 +549,43 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
       uint32_t h0, l0, h1, l1;
       split2<OP, XLO>(u.x, u.y, &h0, &l0);
       split2<OP, XLO>(u.z, u.w, &h1, &l1);
-      uint32_t* mc = lds + (2 * (t + 1) + NEW) * PAIR + (EDGE != 0 ? mwf[f] : mwo + f * kPairHalfDw);
+      uint32_t* mc = lds + (t + 1) * PAIR + (EDGE != 0 ? mwf[f] : mwo + f * kPairHalfDw);
       *reinterpret_cast<uint2*>(mc) = make_uint2(h0, h1);
       if constexpr (XLO) *reinterpret_cast<uint2*>(mc + 2 * LINE) = make_uint2(l0, l1);
     };
-    if constexpr (R == 1) {
-      f32x4 sum[T][2];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) emit(t, f, acc[t][f].s[S]);
+    stage(lds, stg[1 - NEW]);  // input pair P + 1
+    load(stg[1 - NEW]);        // input pair P + 3
+    wave_lds_sync();           // the pairs written are visible
+    if constexpr (R == 3) {
 #pragma unroll
       for (int t = 0; t < T; ++t)
 #pragma unroll
-        for (int f = 0; f < 2; ++f) sum[t][f] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bq[t][f][0]);
-      if constexpr (XLO) {
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-          for (int f = 0; f < 2; ++f) sum[t][f] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), sum[t][f], A, bq[t][f][NS - 1]);
-      }
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int f = 0; f < 2; ++f) sum[t][f] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), sum[t][f], A, bq[t][f][0]);
-      if constexpr (XLO) {
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-          for (int f = 0; f < 2; ++f) sum[t][f] = quad_mma<OP, R, 1>(NEW ^ quad_parity<R, T>(t), sum[t][f], A, bq[t][f][NS - 1]);
-      }
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int f = 0; f < 2; ++f) emit(t, f, sum[t][f]);
-    } else {
-      constexpr int S = 1 - NEW;
-      auto each = [&](auto kc, int s) {
-        constexpr int K = decltype(kc)::value;
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-#pragma unroll
-          for (int f = 0; f < 2; ++f) acc[t][f].s[S] = quad_mma<OP, R, K>(NEW ^ quad_parity<R, T>(t), acc[t][f].s[S], A, bq[t][f][s]);
-      };
-      each(std::integral_constant<int, 2>{}, 0);
-      if constexpr (XLO) each(std::integral_constant<int, 2>{}, NS - 1);
-      each(std::integral_constant<int, 3>{}, 0);
-      if constexpr (XLO) each(std::integral_constant<int, 3>{}, NS - 1);
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int f = 0; f < 2; ++f) {
-          emit(t, f, acc[t][f].s[S]);
+        for (int f = 0; f < 2; ++f)
           acc[t][f].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bq[t][f][0]);
-        }
       if constexpr (XLO) each(std::integral_constant<int, 0>{}, NS - 1);
       each(std::integral_constant<int, 1>{}, 0);
       if constexpr (XLO) each(std::integral_constant<int, 1>{}, NS - 1);
     }
+    // each level's lines of the next iteration replace the older pair of its operands
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      gather(t, 0, 1 - NEW);
+      gather(t, 1, 1 - NEW);
+    }
+    if constexpr (R == 3) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 2 * T * (2 * NS - 1), 0);
+#pragma unroll
+      for (int i = 0; i < 2 * T; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * NS, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // (the next iteration's products would take these places)
+    }
+    wave_lds_sync();
   };
   for (int P = 0; P < nit; P += 2) {
     iter(P, std::integral_constant<int, 0>{});
@@ -596,7 +597,7 @@ template <int R, int OP, int ENG, bool ALIGNED, bool XLO, int T>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((ENG == 1 && T == 1) ? (ALIGNED ? 4 : 3) : 2)))
 void band2d_pair_f32_kernel(BandGrid g) {
   constexpr int PAIRSZ = 2 * (XLO ? 2 : 1) * kPairRowDw;
-  __shared__ uint32_t lds[2 * T * PAIRSZ];
+  __shared__ uint32_t lds[(use_quad<R, ENG>() ? T : 2 * T) * PAIRSZ];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
   // interior waves (every staged column and rows [y0 - T r, y0 + hrows + T r + 2) inside
   // the grid) skip the zeroing of intermediate values outside it; only the waves at
