@@ -25,6 +25,7 @@ struct spider_plan_s {
   int stream_h[4] = {};      //   rows per wave of launches of 1, 2, 4 and 8 steps
   int direct_tile = 32;      // direct engine, several steps per launch: output tile side (16 or 32)
   bool line_deep = false;    // 1-D line whose loops run in LDS, many steps per launch
+  bool auto_rows = false;    // 2-D matrix plan with automatic depth and height: rows from the launch model
   int ncu = 256;             // compute units of the plan's device
   bool tune_depth = false;   // the autotuner also chooses time_block (2..max_time_block)
   int tile_h = 0;

@@ -567,7 +567,8 @@ spider_status enqueue_round(spider_server_s* S, ServerRound& R) {
   for (size_t i = 0; i < R.reqs.size(); ++i) {
     ServerRequest* r = R.reqs[i];
     const spider_impl::BatchItem it{r->plan, r->issued ? r->out : r->in, r->out, r->scratch, R.adv[i]};
-    if ((r->plan->time_block > 2 && r->plan->ndim == 2) || runs_alone(r->plan))
+    const bool large = r->plan->ndim == 2 && (long long)r->plan->ny * r->plan->nx >= (1LL << 23);
+    if ((r->plan->time_block > 2 && large) || runs_alone(r->plan))
       solo.push_back(it);
     else
       groups[(r->plan->operand * 8 + r->plan->engine) * 4 + r->plan->ndim].push_back(it);

@@ -52,6 +52,8 @@ size_t dtype_bytes(int dt) {
   }
 }
 
+static int model_rows_2d(const spider_plan_s* p, int T, long long nstrips, int max_waves);
+
 // Segment height of the 2-D band kernel: enough rows per wave that one launch
 // fills every CU once (all waves resident, no tail round), but not fewer than
 // 16 rows so the 2r halo rows stay a small fraction of the streamed rows.
@@ -66,6 +68,7 @@ static int auto_tile_h_2d(const spider_plan_s* p) {
   const long long slots = (long long)ncu * per_cu;
   const long long nstrips = p->band_h == 8 ? (p->nx + kPairWinLead + kStripWPair - 1) / kStripWPair
                                            : (p->nx + 8 + kStripW - 1) / kStripW;
+  if (p->auto_rows) return model_rows_2d(p, 1, nstrips, per_cu / 4);
   // segments per strip that keep every wave resident: ceil(ny / h) * nstrips <= slots
   const long long segs = std::max<long long>(1, slots / nstrips);
   long long h = (p->ny + segs - 1) / segs;
@@ -268,6 +271,49 @@ void set_tile2(spider_plan_s* p, int h) {
   p->grid_tb2.nblocks = p->grid_tb2.nstrips * p->grid_tb2.nsegs_y;
 }
 
+// Iterations (line pairs, or lines) that a wave of the 2-D band kernels streams for
+// a segment of h rows at T steps per launch.
+static int band2d_iterations(const spider_plan_s* p, int T, int h) {
+  if (p->band_h != 8) {
+    const int rr = 2 * p->r + 1, u = rr >= 5 ? rr : 2 * rr;  // whole turns of the accumulators
+    return (h + 2 * p->r + u - 1) / u * u;
+  }
+  const int np = p->r + 1, up = np >= 3 ? np : 2 * np;
+  return ((h + 1) / 2 + T * p->r + T - 1 + up - 1) / up * up;
+}
+
+// Rows per wave of an automatic 2-D plan's launch of T steps over `nstrips` strips.
+// A lone wave per SIMD takes as long per iteration as its own chain of gathers,
+// products and conversions; a second one stretches both to about 1.6 times that
+// (1.45 with r = 1, whose iterations are the shortest), and so on.  Of the
+// heights that put k = 1 .. 4 waves on a SIMD the one with the smallest iterations
+// times stretch is taken, and among heights of as many iterations the tallest.
+// Box-2D49P fp16, us per step: 512^2 3.2 at 8 rows (4.8 at 32), 1024^2 3.6 (4.9),
+// 10240^2 35.4 at 232 rows and two waves (40.3 at 468 and one, 38.5 at 156, 40.9 at
+// 224: a few more segments than the chip holds two waves of).  Box-2D9P fp16, 4096^2:
+// 6.2 at 40 rows and two waves, 6.7 at 72 and one.
+static int model_rows_2d(const spider_plan_s* p, int T, long long nstrips, int max_waves) {
+  static const double stretches[2][4] = {{1.0, 1.6, 2.3, 3.0}, {1.0, 1.45, 2.15, 2.85}};
+  const double* stretch = stretches[p->r == 1];
+  const int unit = p->band_h == 8 ? 4 : 1;
+  const int top = (p->ny + unit - 1) / unit * unit;
+  int best = top;
+  double best_cost = 1e300;
+  for (int k = 1; k <= std::min(4, max_waves); ++k) {
+    const long long segs = std::max<long long>(1, 4LL * k * p->ncu / nstrips);
+    int h = (int)((p->ny + segs - 1) / segs);
+    h = std::min((h + unit - 1) / unit * unit, top);
+    const int it = band2d_iterations(p, T, h);
+    while (h + unit <= top && band2d_iterations(p, T, h + unit) == it) h += unit;
+    const double cost = it * stretch[k - 1];
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = h;
+    }
+  }
+  return best;
+}
+
 // Segment height of the fused kernel: one resident round, at least 32 rows
 // (its halo is 2 T r lines).
 static int auto_tile_h_tb2(const spider_plan_s* p) {
@@ -310,6 +356,7 @@ static int auto_tile_h_tb2(const spider_plan_s* p) {
                : p->time_block > 2 ? band2d_pair_tbt_blocks_per_cu(p->r, p->operand, p->engine, p->time_block)
                                    : band2d_pair_tb2_blocks_per_cu(p->r, p->operand, p->engine);
   if (per_cu <= 0) per_cu = 8;
+  if (p->auto_rows) return model_rows_2d(p, p->time_block, p->grid_tb2.nstrips, per_cu / 4);
   // a third wave per SIMD adds less than the taller segments of two save in halo
   // rows (two fused steps, paired bands: Box-2D49P 10240^2 1792 GStencil/s at three
   // waves per SIMD, 2067 at two; Star-2D13P 8192^2 1780 against 2064)
@@ -753,6 +800,7 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     // Offline transformation, one kernel row (line of taps along x) at a time, or
     // (paired-line bands) one instruction of r + 1 per input line pair.
     const bool pair = p->band_h == 8;
+    p->auto_rows = ndim == 2 && o.time_block == 0 && o.tile_h == 0 && !o.row_swap;
     const int nrows = pair ? radius + 1 : (ndim == 1 ? 1 : (ndim == 2 ? kw : kw * kw));
     p->nrows = nrows;
     std::vector<PackedRow> rows(nrows);
@@ -839,6 +887,21 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
       T = ndim == 3   ? 1
           : ndim == 1 ? (pts >= (1LL << 22) ? 4 : 2)
                       : (pts >= (1LL << 25) ? 4 : pts >= (1LL << 23) ? 3 : 2);
+      // Odd radii on the sparse engine have cheaper levels: with r = 1 four steps pay from
+      // 2^19 points (1024^2 2.4 us per step against 2.7 at two, 4096^2 6.1 against 7.0 at
+      // three), with r = 3 from 2^22 (2048^2 4.8 against 5.2; at 2^23 .. 2^24 three are as
+      // fast); four steps round as two launches of two do.  fp32 carry: three from 2^22
+      // points.  r = 2 stops at three (8192^2 22.5 against 24.5 at four).
+      if (ndim == 2 && pair && engine == SPIDER_ENGINE_SPARSE) {
+        if (radius == 2)
+          T = std::min(T, 3);
+        else if (!low)
+          T = pts >= (1LL << 22) ? 3 : T;
+        else if (radius == 1)
+          T = pts >= (1LL << 19) ? 4 : T;
+        else
+          T = pts >= (1LL << 22) && (pts < (1LL << 23) || pts >= (1LL << 24)) ? 4 : T;
+      }
       p->line_deep = tb1_ok && o.tile_h == 0;
       p->tune_depth = o.autotune && o.tile_h == 0 && p->max_time_block > 2 && !p->line_deep;
     } else {
