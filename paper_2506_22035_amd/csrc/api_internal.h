@@ -47,9 +47,10 @@ struct spider_plan_s {
   int tile_h2 = 0;                      // segment height of the fused kernel
   spider_impl::BandGrid grid_tb2{};     // fused kernel: 240-wide strips (two steps) or pair_tb_width
   spider_impl::BandGrid grid_rem2{};    // time_block > 2: two-step kernel for a remainder of 2 or 3 steps
-  spider_impl::BandGrid grid_batch{};   // one-step kernel inside batched launches (taller segments)
-  spider_impl::BandGrid grid_batch2{};  // two fused steps inside batched launches (paired bands)
-  bool batch_fuse = false;              // grid_batch2 is set: batches advance this grid two steps per launch
+  // batched launches (segment heights are chosen per launch): one step, two and four fused
+  // steps; batch_fuse: the most steps per launch (1, 2 on paired bands, 4 on quads)
+  spider_impl::BandGrid grid_batch{}, grid_batch2{}, grid_batch4{};
+  int batch_fuse = 1;
   hipStream_t cap_stream = nullptr;
   std::map<std::tuple<const void*, const void*, int>, hipGraphExec_t> graphs;
   // long time loops: one graph of kGraphBody launches of one kind (steps per launch)

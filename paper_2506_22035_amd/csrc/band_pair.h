@@ -717,6 +717,21 @@ __device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint3
   }
 }
 
+// The quad body for what wave w computes beyond the grid.  ALIGNED = false: some widths
+// are not multiples of 8, and the waves at the end of such lines run the ragged body.
+template <int R, int OP, bool ALIGNED, int T>
+__device__ __forceinline__ void quad_bodies(const BandGrid& g, int w, uint32_t* lds) {
+  const int edge = quad_edge<R, T>(g, w, true);
+  if (!ALIGNED && g.nx % 8 != 0 && !pair_inside(g, w, quad_width(T, R), quad_margin(T, R)))
+    band2d_quad_body<R, OP, ALIGNED, T, 2>(g, w, lds);
+  else if (edge == 0)
+    band2d_quad_body<R, OP, true, T, 0>(g, w, lds);
+  else if (edge == 1)
+    band2d_quad_body<R, OP, true, T, 1>(g, w, lds);
+  else
+    band2d_quad_body<R, OP, true, T, 2>(g, w, lds);
+}
+
 // The body of a paired-band step (T = 1) or of T fused ones for radius R.
 template <int R, int ENG>
 constexpr bool use_quad() {

@@ -1,7 +1,7 @@
 // Batched time loop over many grids and the continuous-batching server.
 //
 // Batching is not in the paper (it evaluates one grid at a time); it serves
-// many grids of uneven size and stencil shape with one launch per time step,
+// many grids of uneven size and stencil shape with one launch per one to four time steps,
 // one workgroup per (grid, strip, segment) work unit, each workgroup finding
 // its grid by binary search over the units' prefix sums.  (A persistent
 // variant, in which resident workgroups pulled units from device counters,
@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -89,8 +90,9 @@ struct BatchArena {
   }
 };
 
-static int batch_kind(const spider_plan_s* p, bool fused) {
-  if (fused) return p->r == 1 ? kB2dPairTb2R1 : (p->r == 2 ? kB2dPairTb2R2 : kB2dPairTb2R3);
+static int batch_kind(const spider_plan_s* p, int T) {
+  if (T == 4) return p->r == 1 ? kB2dPairTb4R1 : kB2dPairTb4R3;
+  if (T == 2) return p->r == 1 ? kB2dPairTb2R1 : (p->r == 2 ? kB2dPairTb2R2 : kB2dPairTb2R3);
   if (p->ndim == 2 && p->band_h == 8) return p->r == 1 ? kB2dPairR1 : (p->r == 2 ? kB2dPairR2 : kB2dPairR3);
   if (p->ndim == 2) return p->r == 1 ? kB2dR1 : (p->r == 2 ? kB2dR2 : kB2dR3);
   // 3-D r = 1: star variant when every non-zero kernel row lies on the axes cross
@@ -115,42 +117,72 @@ static int device_cus() {
   return ncu;
 }
 
-static void set_height_3d(BandGrid& g, int h) {
-  h = std::min(h, g.nz);
-  g.seg_h = h;
-  g.nsegs_z = (g.nz + h - 1) / h;
+// Rows (2-D) or planes (3-D) per work unit.
+static void set_height(BandGrid& g, int ndim, int h) {
+  if (ndim == 3) {
+    g.seg_h = std::min(h, g.nz);
+    g.nsegs_z = (g.nz + g.seg_h - 1) / g.seg_h;
+  } else {
+    g.seg_h = std::min(h, (g.ny + 3) / 4 * 4);
+    g.nsegs_y = (g.ny + g.seg_h - 1) / g.seg_h;
+  }
   g.nblocks = g.nstrips * g.nsegs_y * g.nsegs_z;
 }
 
-// Segment height (planes) shared by the 3-D grids of one batch.  Tall segments
-// re-read fewer halo planes, and equal heights give units of similar length
-// (a launch lasts as long as its longest units), but the launch still needs
-// 4 units per CU to fill the device: the tallest height up to 64 planes for
-// which the batch's first step has that many units.
-static int batch_height_3d(const std::vector<BatchItem>& items) {
-  long long fixed = 0;
-  bool any3 = false;
-  for (const auto& it : items) {
-    if (it.steps <= 0) continue;
-    if (it.plan->ndim == 3) any3 = true;
-    else fixed += it.plan->grid_batch.nblocks;
-  }
-  if (!any3) return 64;
-  const long long want = 4LL * device_cus();
-  for (int h = 64; h > 1; --h) {
-    long long units = fixed;
-    for (const auto& it : items) {
-      if (it.steps <= 0 || it.plan->ndim != 3) continue;
-      BandGrid g = it.plan->grid_batch;
-      set_height_3d(g, h);
-      units += g.nblocks;
-    }
-    if (units >= want) return h;
-  }
-  return 1;
+// One grid's part of one launch: its geometry and steps.
+struct LaunchPart {
+  const spider_plan_s* plan;
+  const BandGrid* geom;
+  int T;
+};
+
+// Time a wave alone on its SIMD takes for a unit of h rows or planes (us).
+static double unit_time(const LaunchPart& u, int h) {
+  const spider_plan_s* p = u.plan;
+  if (p->ndim == 3) return 0.62 * ((std::min(h, p->nz) + 4) / 3 * 3);  // planes, in whole turns of three
+  h = std::min(h, p->ny);
+  if (p->band_h != 8) return 0.2 * (h + 2 * p->r);
+  const int np = p->r + 1, up = np >= 3 ? np : 2 * np;  // line pairs, in whole bodies
+  const int it = ((h + 1) / 2 + u.T * p->r + u.T - 1 + up - 1) / up * up;
+  return it * (0.10 + (p->r == 1 ? 0.075 : 0.095) * u.T);
 }
 
-// A batched time loop laid out for the device: the per-launch descriptors
+// Common height of a launch's units.  A launch lasts as long as its longest chain, and
+// waves that share a SIMD stretch each other: by 0.6 of a wave's time each in 2-D, 0.85
+// in 3-D, whose waves wait less for their own results.  Short units fill the device and
+// have short chains, tall ones compute fewer halo lines twice.  (A round of a dozen
+// requests, sides 512 .. 4096 and 64 .. 256, 1 .. 100 steps: 3508 us at a fixed 64 rows
+// and two steps per launch, both dimensions in one launch; 1231 now.)
+static int launch_height(const std::vector<LaunchPart>& parts, int ndim) {
+  const double simds = 4.0 * device_cus(), share = ndim == 3 ? 0.85 : 0.6, fixed = 2.3;
+  const int first = ndim == 3 ? 1 : 8, step = ndim == 3 ? 3 : 4, top = ndim == 3 ? 64 : 256;
+  int best = first;
+  double best_cost = 1e300;
+  for (int h = first; h <= top; h += step) {
+    double longest = 0, total = 0;
+    long long units = 0;
+    for (const auto& u : parts) {
+      BandGrid g = *u.geom;
+      set_height(g, ndim, h);
+      const double t = unit_time(u, g.seg_h);
+      longest = std::max(longest, t);
+      total += t * g.nblocks;
+      units += g.nblocks;
+    }
+    // (large volumes are bound by memory, where tall segments re-read the fewest planes)
+    if (ndim == 3 && h == top && units >= 2 * simds) return h;
+    double k = total / (simds * longest);
+    if (k <= 4.0) k = std::ceil(k);
+    const double cost = fixed + longest * (1.0 + share * std::max(0.0, k - 1.0));
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = h;
+    }
+  }
+  return best;
+}
+
+// A batched time loop of grids of one dimension laid out for the device: the per-launch descriptors
 // (BandGrid[m] | int kinds[m] | int begin[m + 1], 256-byte aligned blocks), the
 // work units of each launch, and the device-to-device copies that precede it
 // (steps == 0 results, and in == out sources that the first launch must not
@@ -168,7 +200,7 @@ struct BatchProgram {
   std::vector<Copy> copies;
 };
 
-// Lay out the batched time loop of `items`.
+// Lay out the batched time loop of `items` (2-D grids or 3-D grids, not both).
 static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgram* prog) {
   const int n = (int)items.size();
   BatchProgram& P = *prog;
@@ -189,22 +221,22 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
     if (it.steps < 0) return fail(SPIDER_ERR_INVALID, "steps must be >= 0");
     maxsteps = std::max(maxsteps, it.steps);
   }
-  // the kernel variant holding only the body classes present (2-D: 1, 3-D: 2)
+  const int ndim = items[0].plan->ndim;
   bool aligned = true;
-  for (const auto& it : items) {
-    P.cls |= it.plan->ndim == 3 ? 2 : 1;
-    aligned = aligned && it.plan->nx % 8 == 0;
-  }
-  if (aligned) P.cls |= 4;  // aligned bodies only
-  // Per item: its launches (grids with paired bands run steps / 2 launches of two
-  // fused steps, then a single step if steps is odd, as spider_apply with
-  // time_block 2 does), and the first source, after the in == out copy when needed.
-  std::vector<int> nl(n), nf(n);
+  for (const auto& it : items) aligned = aligned && it.plan->nx % 8 == 0;
+  P.cls = (ndim == 3 ? 2 : 1) + (aligned ? 4 : 0);
+  // Per item: its launches of four, two and one step, deepest first (every depth rounds
+  // as single steps of two do), and the first source, after the in == out copy when needed.
+  std::vector<int> nl(n), n4(n), n2(n);
   int maxl = 0;
   for (int i = 0; i < n; ++i) {
-    const BatchItem& it = items[i];
-    nf[i] = it.plan->batch_fuse ? it.steps / 2 : 0;
-    nl[i] = nf[i] + (it.steps - 2 * nf[i]);
+    const int fuse = items[i].plan->batch_fuse;
+    int left = items[i].steps;
+    n4[i] = fuse >= 4 ? left / 4 : 0;
+    left -= 4 * n4[i];
+    n2[i] = fuse >= 2 ? left / 2 : 0;
+    left -= 2 * n2[i];
+    nl[i] = n4[i] + n2[i] + left;
     maxl = std::max(maxl, nl[i]);
   }
   std::vector<const void*> cur(n);
@@ -220,7 +252,6 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
     }
   }
   if (maxsteps == 0) return SPIDER_OK;
-  const int h3 = batch_height_3d(items);
   P.off.assign(maxl + 1, 0);
   P.m.assign(maxl, 0);
   P.units.assign(maxl, 0);
@@ -234,25 +265,38 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
   }
   P.off[maxl] = bytes;
   P.desc.assign(bytes, 0);
+  std::vector<LaunchPart> parts, last;
+  int height = 0;
   for (int st = 0; st < maxl; ++st) {
     char* base = P.desc.data() + P.off[st];
     BandGrid* gd = reinterpret_cast<BandGrid*>(base);
     int* kinds = reinterpret_cast<int*>(base + P.m[st] * sizeof(BandGrid));
     int* begin = kinds + P.m[st];
+    parts.clear();
+    for (int i = 0; i < n; ++i) {
+      if (nl[i] <= st) continue;
+      const spider_plan_s* p = items[i].plan;
+      const int T = st < n4[i] ? 4 : st < n4[i] + n2[i] ? 2 : 1;
+      parts.push_back({p, T == 4 ? &p->grid_batch4 : T == 2 ? &p->grid_batch2 : &p->grid_batch, T});
+    }
+    // (the same grids at the same depths as in the launch before have the same height)
+    bool same = parts.size() == last.size();
+    for (size_t i = 0; same && i < parts.size(); ++i) same = parts[i].geom == last[i].geom;
+    if (!same) height = launch_height(parts, ndim);
+    last = parts;
     int j = 0, acc = 0;
     for (int i = 0; i < n; ++i) {
       const BatchItem& it = items[i];
       if (nl[i] <= st) continue;
       const int k = st + 1;
       void* dst = ((nl[i] - k) % 2 == 0) ? it.out : it.scratch;
-      const bool fused = st < nf[i];
-      BandGrid g = fused ? it.plan->grid_batch2 : it.plan->grid_batch;
-      if (it.plan->ndim == 3) set_height_3d(g, h3);
+      BandGrid g = *parts[j].geom;
+      set_height(g, ndim, height);
       g.in = cur[i];
       g.out = dst;
       cur[i] = dst;
       gd[j] = g;
-      kinds[j] = batch_kind(it.plan, fused);
+      kinds[j] = batch_kind(it.plan, parts[j].T);
       begin[j] = acc;
       acc += g.nblocks;
       ++j;
@@ -264,11 +308,28 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
   return SPIDER_OK;
 }
 
-static spider_status enqueue_copies(const BatchProgram& P, hipStream_t s) {
-  for (const auto& c : P.copies) {
-    hipError_t e = hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
+// The batched time loops of `items`: one of the 2-D grids and one of the 3-D grids.  A
+// launch of one dimension holds only its own bodies and registers, and its height suits
+// its own grids; the two loops do not depend on each other.
+static spider_status build_batches(const std::vector<BatchItem>& items, std::vector<BatchProgram>* progs) {
+  for (int ndim = 1; ndim <= 3; ++ndim) {
+    std::vector<BatchItem> part;
+    for (const auto& it : items)
+      if (it.plan->ndim == ndim) part.push_back(it);
+    if (part.empty()) continue;
+    progs->emplace_back();
+    const spider_status st = build_batch(part, &progs->back());
+    if (st != SPIDER_OK) return st;
   }
+  return SPIDER_OK;
+}
+
+static spider_status enqueue_copies(const std::vector<BatchProgram>& progs, hipStream_t s) {
+  for (const auto& P : progs)
+    for (const auto& c : P.copies) {
+      hipError_t e = hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToDevice, s);
+      if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
+    }
   return SPIDER_OK;
 }
 
@@ -288,19 +349,29 @@ static spider_status enqueue_launches(const BatchProgram& P, const char* dev, hi
 // Enqueue the batched time loop of `items` on stream s, its descriptors staged
 // through the arena.
 spider_status enqueue_batch(BatchArena& A, const std::vector<BatchItem>& items, hipStream_t s) {
-  BatchProgram P;
-  spider_status st = build_batch(items, &P);
+  std::vector<BatchProgram> progs;
+  spider_status st = build_batches(items, &progs);
   if (st != SPIDER_OK) return st;
-  st = enqueue_copies(P, s);
-  if (st != SPIDER_OK || P.m.empty()) return st;
-  const size_t bytes = P.desc.size();
+  st = enqueue_copies(progs, s);
+  size_t bytes = 0;
+  for (const auto& P : progs) bytes += P.desc.size();
+  if (st != SPIDER_OK || bytes == 0) return st;
   std::lock_guard<std::mutex> lk(A.mu);
   hipError_t e = A.reserve(bytes);
   if (e != hipSuccess) return hip_fail(e, "batch descriptor buffers");
-  std::memcpy(A.host, P.desc.data(), bytes);
+  size_t at = 0;
+  for (const auto& P : progs) {
+    std::memcpy(A.host + at, P.desc.data(), P.desc.size());
+    at += P.desc.size();
+  }
   e = hipMemcpyAsync(A.dev, A.host, bytes, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail(e, "descriptor upload");
-  st = enqueue_launches(P, A.dev, s);
+  at = 0;
+  for (const auto& P : progs) {
+    st = enqueue_launches(P, A.dev + at, s);
+    if (st != SPIDER_OK) break;
+    at += P.desc.size();
+  }
   if (st != SPIDER_OK) return st;
   e = hipEventRecord(A.done, s);
   if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -325,7 +396,21 @@ struct BatchGraphEntry {
 constexpr size_t kBatchGraphs = 32;
 std::mutex g_bg_mu;
 std::vector<BatchGraphEntry> g_bg;  // oldest first
-std::map<int, hipStream_t> g_bg_capture;  // capture stream per device
+// per device: the capture stream, a second one for the loop that runs beside the first,
+// and the events that fork and join it
+struct BatchCapture {
+  hipStream_t main = nullptr, side = nullptr;
+  hipEvent_t fork = nullptr, join = nullptr;
+  hipError_t create() {
+    hipError_t e = hipSuccess;
+    if (!main) e = hipStreamCreateWithFlags(&main, hipStreamNonBlocking);
+    if (e == hipSuccess && !side) e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
+    if (e == hipSuccess && !fork) e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
+    if (e == hipSuccess && !join) e = hipEventCreateWithFlags(&join, hipEventDisableTiming);
+    return e;
+  }
+};
+std::map<int, BatchCapture> g_bg_capture;
 
 void release_entry(BatchGraphEntry& en) {
   int cur = 0;
@@ -362,27 +447,48 @@ static spider_status enqueue_batch_graph(const std::vector<BatchItem>& items, in
   for (auto& en : g_bg)
     if (en.device == device && en.key == key) hit = &en;
   if (!hit) {
-    BatchProgram P;
-    spider_status st = build_batch(items, &P);
+    std::vector<BatchProgram> progs;
+    spider_status st = build_batches(items, &progs);
     if (st != SPIDER_OK) return st;
     BatchGraphEntry en;
     en.key = key;
     en.device = device;
-    en.copies = P.copies;
-    if (!P.m.empty()) {
-      hipError_t e = hipMalloc(&en.dev_desc, P.desc.size());
+    std::vector<char> desc;
+    std::vector<std::pair<const BatchProgram*, size_t>> loops;  // time loops and their descriptors' offsets
+    for (const auto& P : progs) {
+      en.copies.insert(en.copies.end(), P.copies.begin(), P.copies.end());
+      if (P.m.empty()) continue;
+      loops.emplace_back(&P, desc.size());
+      desc.insert(desc.end(), P.desc.begin(), P.desc.end());
+    }
+    if (!loops.empty()) {
+      hipError_t e = hipMalloc(&en.dev_desc, desc.size());
       if (e != hipSuccess) return fail(SPIDER_ERR_OOM, "batch graph descriptors: %s", hipGetErrorString(e));
-      e = hipMemcpy(en.dev_desc, P.desc.data(), P.desc.size(), hipMemcpyHostToDevice);
-      hipStream_t& cs = g_bg_capture[device];
-      if (e == hipSuccess && !cs) e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-      if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+      e = hipMemcpy(en.dev_desc, desc.data(), desc.size(), hipMemcpyHostToDevice);
+      BatchCapture& cap = g_bg_capture[device];
+      if (e == hipSuccess) e = cap.create();
+      if (e == hipSuccess) e = hipStreamBeginCapture(cap.main, hipStreamCaptureModeThreadLocal);
       if (e != hipSuccess) {
         (void)hipFree(en.dev_desc);
         return hip_fail(e, "batch graph set-up");
       }
-      st = enqueue_launches(P, en.dev_desc, cs);
+      // The loops of the two dimensions are independent branches: short launches of the
+      // one fill what those of the other leave idle.
+      const bool fork = loops.size() > 1;
+      hipError_t fe = hipSuccess;
+      if (fork) {
+        fe = hipEventRecord(cap.fork, cap.main);
+        if (fe == hipSuccess) fe = hipStreamWaitEvent(cap.side, cap.fork, 0);
+      }
+      for (size_t i = 0; i < loops.size() && fe == hipSuccess && st == SPIDER_OK; ++i)
+        st = enqueue_launches(*loops[i].first, en.dev_desc + loops[i].second, i ? cap.side : cap.main);
+      if (fork && fe == hipSuccess) {
+        fe = hipEventRecord(cap.join, cap.side);
+        if (fe == hipSuccess) fe = hipStreamWaitEvent(cap.main, cap.join, 0);
+      }
       hipGraph_t graph = nullptr;
-      e = hipStreamEndCapture(cs, &graph);
+      e = hipStreamEndCapture(cap.main, &graph);
+      if (e == hipSuccess) e = fe;
       if (st == SPIDER_OK && e == hipSuccess) e = hipGraphInstantiate(&en.exec, graph, nullptr, nullptr, 0);
       if (graph) (void)hipGraphDestroy(graph);
       if (st != SPIDER_OK || e != hipSuccess) {
@@ -555,11 +661,9 @@ struct ServerRound {
 };
 
 // Enqueue one round: every listed request advances by its step count, one batched
-// time loop per (operand dtype, engine, dimension) group: a launch of one dimension
-// runs the single-class batch kernel, which keeps more waves per SIMD than the
-// kernel holding both the 2-D and 3-D bodies (7-8 % more requests per second on the
-// serving mix than one mixed launch).  Grids whose plan fuses more than the batched
-// launch's two steps (large 2-D grids), and plans the batched kernel does not hold,
+// time loop per (operand dtype, engine, dimension) group (a launch of one dimension holds
+// only its own bodies and registers).  Large 2-D grids whose plan fuses more than two
+// steps, which fill the device by themselves, and plans the batched kernel does not hold
 // run their own launches instead, with the request's scratch buffer.
 spider_status enqueue_round(spider_server_s* S, ServerRound& R) {
   std::map<int, std::vector<spider_impl::BatchItem>> groups;

@@ -149,17 +149,17 @@ int band3d_tb2_blocks_per_cu(int r, int operand, int engine, uint32_t rowmask);
 enum BatchKind : int {
   kB2dR1 = 0, kB2dR2 = 1, kB2dR3 = 2, kB3dBox = 3, kB3dStar = 4,
   kB2dPairR1 = 5, kB2dPairR2 = 6, kB2dPairR3 = 7,      // paired-line bands (one step)
-  kB2dPairTb2R1 = 8, kB2dPairTb2R2 = 9, kB2dPairTb2R3 = 10  // paired-line bands, two fused steps
+  kB2dPairTb2R1 = 8, kB2dPairTb2R2 = 9, kB2dPairTb2R3 = 10,  // paired-line bands, two fused steps
+  kB2dPairTb4R1 = 11, kB2dPairTb4R3 = 12  // four fused steps (sparse engine)
 };
 
-// One launch advancing every listed grid by one time step.
+// One launch advancing every listed grid by the steps of its kind.
 //   grids    device array of n BandGrid (in/out already set for this step)
 //   kinds    device array of n BatchKind
 //   begin    device array of n+1 prefix sums of grids[i].nblocks
 //   units    begin[n] (host copy): one workgroup per work unit
-// cls: bodies compiled into the launched kernel, 1 = 2-D kinds only, 2 = 3-D kinds
-// only, 3 = both (a batch of one class gets a smaller register budget per wave);
-// + 4 when every grid's row length is a multiple of 8 (aligned bodies only).
+// cls: the kinds of the launch, 1 = 2-D, 2 = 3-D, + 4 when every grid's row length is a
+// multiple of 8 (aligned bodies only).
 hipError_t launch_band_batch(int operand, int engine, int cls, const BandGrid* grids, const int* kinds,
                              const int* begin, int n, int units, hipStream_t s);
 

@@ -1221,39 +1221,33 @@ int band2d_blocks_per_cu(int r, int operand, int engine, bool aligned) {
 
 // ----------------------------------------------------------------------------- batched
 
-// A paired-band unit: one step, or two fused ones.
-template <int R, int OP, int ENG>
-__device__ __forceinline__ void batch_pair(const BandGrid& g, int w, uint32_t* lds, bool al, bool two) {
+// A paired-band unit of T = 1, 2 or 4 steps.
+template <int R, int OP, int ENG, bool AL_ONLY, int T>
+__device__ __forceinline__ void batch_pair(const BandGrid& g, int w, uint32_t* lds, bool al) {
   if constexpr (use_quad<R, ENG>()) {
-    if (two) {
-      if (al) band2d_quad_body<R, OP, true, 2, 2>(g, w, lds);
-      else band2d_quad_body<R, OP, false, 2, 2>(g, w, lds);
-    } else {
-      if (al) band2d_quad_body<R, OP, true, 1, 0>(g, w, lds);
-      else band2d_quad_body<R, OP, false, 1, 2>(g, w, lds);
-    }
-  } else {
-    if (two) {
-      if (al) band2d_pair_tb2_body<R, OP, ENG, true, true>(g, w, lds);
-      else band2d_pair_tb2_body<R, OP, ENG, false, true>(g, w, lds);
-    } else {
-      if (al) band2d_pair_body<R, OP, ENG, true>(g, w, lds);
-      else band2d_pair_body<R, OP, ENG, false>(g, w, lds);
-    }
+    quad_bodies<R, OP, AL_ONLY, T>(g, w, lds);
+  } else if constexpr (T == 2) {
+    if (al) band2d_pair_tb2_body<R, OP, ENG, true, true>(g, w, lds);
+    else band2d_pair_tb2_body<R, OP, ENG, false, true>(g, w, lds);
+  } else if constexpr (T == 1) {
+    if (al) band2d_pair_body<R, OP, ENG, true>(g, w, lds);
+    else band2d_pair_body<R, OP, ENG, false>(g, w, lds);
   }
 }
 
 // One workgroup per work unit (a strip segment of one grid); the launch has
 // exactly begin[n] workgroups.  CLS selects the bodies compiled in: 1 = 2-D
-// kinds, 2 = 3-D kinds, 3 = all.
+// kinds, 2 = 3-D kinds.  Four fused steps need the registers of two waves per SIMD.
 template <int OP, int ENG, int CLS>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(((CLS == 5 || CLS == 6) && ENG == 1) ? 3 : 2))) void band_batch_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((CLS & 2) && ENG == 1 ? 3 : 2))) void band_batch_kernel(
     const BandGrid* __restrict__ grids, const int* __restrict__ kinds, const int* __restrict__ begin, int n) {
   // CLS bit 4: every grid's row length is a multiple of 8, so only the aligned
   // bodies are compiled in (the unaligned ones need more registers)
   constexpr bool k2d = (CLS & 1) != 0, k3d = (CLS & 2) != 0, al_only = (CLS & 4) != 0;
-  // the largest body: 16-point r = 3 (7 lines + spare) or two fused paired steps (12 lines)
-  constexpr int kLds = (7 * kLdsRowDw + kLdsSpareDw) > (12 * kPairRowDw) ? (7 * kLdsRowDw + kLdsSpareDw) : (12 * kPairRowDw);
+  // 3-D: the lines of a plane; 2-D, the largest body: 16-point r = 3 (7 lines + spare) or
+  // two fused paired steps (12 lines)
+  constexpr int kBandLds = (k3d ? kRowsY3 + 2 : 7) * kLdsRowDw + kLdsSpareDw;
+  constexpr int kLds = k3d || kBandLds > 12 * kPairRowDw ? kBandLds : 12 * kPairRowDw;
   __shared__ uint32_t lds[kLds];
   const int total = begin[n];
   if ((int)blockIdx.x >= total) return;
@@ -1281,12 +1275,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(((CLS == 5 |
       case kB2dR1: if (al) band2d_body<1, OP, ENG, true>(g, w, lds); else band2d_body<1, OP, ENG, false>(g, w, lds); break;
       case kB2dR2: if (al) band2d_body<2, OP, ENG, true>(g, w, lds); else band2d_body<2, OP, ENG, false>(g, w, lds); break;
       case kB2dR3: if (al) band2d_body<3, OP, ENG, true>(g, w, lds); else band2d_body<3, OP, ENG, false>(g, w, lds); break;
-      case kB2dPairR1: batch_pair<1, OP, ENG>(g, w, lds, al, false); break;
-      case kB2dPairR2: batch_pair<2, OP, ENG>(g, w, lds, al, false); break;
-      case kB2dPairR3: batch_pair<3, OP, ENG>(g, w, lds, al, false); break;
-      case kB2dPairTb2R1: batch_pair<1, OP, ENG>(g, w, lds, al, true); break;
-      case kB2dPairTb2R2: batch_pair<2, OP, ENG>(g, w, lds, al, true); break;
-      case kB2dPairTb2R3: batch_pair<3, OP, ENG>(g, w, lds, al, true); break;
+      case kB2dPairR1: batch_pair<1, OP, ENG, al_only, 1>(g, w, lds, al); break;
+      case kB2dPairR2: batch_pair<2, OP, ENG, al_only, 1>(g, w, lds, al); break;
+      case kB2dPairR3: batch_pair<3, OP, ENG, al_only, 1>(g, w, lds, al); break;
+      case kB2dPairTb2R1: batch_pair<1, OP, ENG, al_only, 2>(g, w, lds, al); break;
+      case kB2dPairTb2R2: batch_pair<2, OP, ENG, al_only, 2>(g, w, lds, al); break;
+      case kB2dPairTb2R3: batch_pair<3, OP, ENG, al_only, 2>(g, w, lds, al); break;
+      case kB2dPairTb4R1: batch_pair<1, OP, ENG, al_only, 4>(g, w, lds, al); break;
+      case kB2dPairTb4R3: batch_pair<3, OP, ENG, al_only, 4>(g, w, lds, al); break;
       default:
         break;
     }
@@ -1309,10 +1305,8 @@ static hipError_t launch_batch_cls(int cls, const BandGrid* grids, const int* ki
   switch (cls) {
     case 1: hipLaunchKernelGGL((band_batch_kernel<OP, ENG, 1>), grid, block, 0, s, grids, kinds, begin, n); break;
     case 2: hipLaunchKernelGGL((band_batch_kernel<OP, ENG, 2>), grid, block, 0, s, grids, kinds, begin, n); break;
-    case 3: hipLaunchKernelGGL((band_batch_kernel<OP, ENG, 3>), grid, block, 0, s, grids, kinds, begin, n); break;
     case 5: hipLaunchKernelGGL((band_batch_kernel<OP, ENG, 5>), grid, block, 0, s, grids, kinds, begin, n); break;
     case 6: hipLaunchKernelGGL((band_batch_kernel<OP, ENG, 6>), grid, block, 0, s, grids, kinds, begin, n); break;
-    case 7: hipLaunchKernelGGL((band_batch_kernel<OP, ENG, 7>), grid, block, 0, s, grids, kinds, begin, n); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1320,7 +1314,7 @@ static hipError_t launch_batch_cls(int cls, const BandGrid* grids, const int* ki
 
 hipError_t launch_band_batch(int operand, int engine, int cls, const BandGrid* grids, const int* kinds,
                              const int* begin, int n, int units, hipStream_t s) {
-  if (cls < 1 || cls > 7 || cls == 4 || units < 1) return hipErrorInvalidValue;
+  if (units < 1) return hipErrorInvalidValue;
   if (operand == 2 && engine == 1) return launch_batch_cls<2, 1>(cls, grids, kinds, begin, n, units, s);
   if (operand == 2 && engine == 2) return launch_batch_cls<2, 2>(cls, grids, kinds, begin, n, units, s);
   if (operand == 3 && engine == 1) return launch_batch_cls<3, 1>(cls, grids, kinds, begin, n, units, s);

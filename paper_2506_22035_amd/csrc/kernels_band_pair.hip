@@ -24,20 +24,6 @@
 
 namespace spider_impl {
 
-// The quad body for what wave w computes beyond the grid.
-template <int R, int OP, bool ALIGNED, int T>
-__device__ __forceinline__ void quad_bodies(const BandGrid& g, int w, uint32_t* lds) {
-  const int edge = quad_edge<R, T>(g, w, true);
-  if (!ALIGNED && !pair_inside(g, w, quad_width(T, R), quad_margin(T, R)))
-    band2d_quad_body<R, OP, ALIGNED, T, 2>(g, w, lds);
-  else if (edge == 0)
-    band2d_quad_body<R, OP, true, T, 0>(g, w, lds);
-  else if (edge == 1)
-    band2d_quad_body<R, OP, true, T, 1>(g, w, lds);
-  else
-    band2d_quad_body<R, OP, true, T, 2>(g, w, lds);
-}
-
 // ALIGNED = false: widths that are not a multiple of 8; only the waves that stage the
 // end of the lines run the ragged bodies.
 template <int R, int OP, int ENG, bool ALIGNED>

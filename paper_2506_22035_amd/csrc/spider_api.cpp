@@ -219,32 +219,12 @@ spider_status launch_step2(spider_plan_s* p, const void* src, void* dst, hipStre
 // are not batched.
 void set_batch_geometry(spider_plan_s* p) {
   p->grid_batch = p->grid_template;
-  if (p->ndim == 1) return;
-  BandGrid& g = p->grid_batch;
-  int hb;
-  if (p->ndim == 2) {
-    // flat in measurements from 32 to 256 rows; 64 keeps the halo share small
-    hb = std::min(p->ny, std::max(p->tile_h, 64));
-    if (p->band_h == 8) hb += hb & 1;
-    g.nsegs_y = (p->ny + hb - 1) / hb;
-    // paired bands with a 16-bit carry: batches run two fused steps per launch
-    p->batch_fuse = p->band_h == 8 && p->carry == p->operand && p->r <= 3 && !p->row_swap;
-    if (p->batch_fuse) {
-      BandGrid& g2 = p->grid_batch2;
-      g2 = p->grid_template;
-      g2.nstrips = (p->nx + kStripW2_host - 1) / kStripW2_host;
-      g2.seg_h = hb;
-      g2.nsegs_y = (p->ny + hb - 1) / hb;
-      g2.nsegs_z = 1;
-      g2.nblocks = g2.nstrips * g2.nsegs_y;
-    }
-  } else {
-    // the batched launch re-chooses one common 3-D height per batch
-    hb = std::min(p->nz, 64);
-    g.nsegs_z = (p->nz + hb - 1) / hb;
-  }
-  g.seg_h = hb;
-  g.nblocks = g.nstrips * g.nsegs_y * g.nsegs_z;
+  p->batch_fuse = 1;
+  if (p->ndim != 2 || p->band_h != 8 || p->carry != p->operand || p->r > 3 || p->row_swap) return;
+  p->batch_fuse = p->engine == SPIDER_ENGINE_SPARSE && p->r != 2 ? 4 : 2;
+  p->grid_batch2 = p->grid_batch4 = p->grid_template;
+  p->grid_batch2.nstrips = (p->nx + kStripW2_host - 1) / kStripW2_host;
+  p->grid_batch4.nstrips = (p->nx + pair_tb_width(4, p->r) - 1) / pair_tb_width(4, p->r);
 }
 
 void set_tile2(spider_plan_s* p, int h) {
