@@ -163,6 +163,11 @@ enum BatchKind : int {
 hipError_t launch_band_batch(int operand, int engine, int cls, const BandGrid* grids, const int* kinds,
                              const int* begin, int n, int units, hipStream_t s);
 
+// Two fused steps of the 2-D band engine at radius 4 .. 7 (16-bit carry, sparse engine):
+// strips as launch_band2d_tb2 (240 stored columns), seg_h rows per wave, at most two
+// waves per SIMD.
+hipError_t launch_band2d_wide2(int r, int operand, const BandGrid& g, hipStream_t s);
+
 // Output rows per 3-D wave along y (accumulator block height).
 constexpr int kRowsY3 = 4;
 

@@ -204,7 +204,8 @@ spider_status launch_step2(spider_plan_s* p, const void* src, void* dst, hipStre
                                                     p->carry != SPIDER_F32)
                             : launch_band1d_tbt(p->r, p->operand, p->engine, p->time_block, g, s))
       : p->ndim == 3 ? launch_band3d_tb2(p->r, p->operand, p->engine, g, s)
-      : p->band_h != 8 ? launch_band2d_tb2(p->r, p->operand, p->engine, g, s)
+      : p->band_h != 8 ? (p->r > 3 ? launch_band2d_wide2(p->r, p->operand, g, s)
+                                   : launch_band2d_tb2(p->r, p->operand, p->engine, g, s))
       : p->carry == SPIDER_F32
           ? launch_band2d_pair_f32(p->r, p->operand, p->engine, p->split == 3, p->time_block, g, s)
       : p->time_block > 2 ? launch_band2d_pair_tbt(p->r, p->operand, p->engine, p->time_block, g, s)
@@ -256,7 +257,7 @@ void set_tile2(spider_plan_s* p, int h) {
 static int band2d_iterations(const spider_plan_s* p, int T, int h) {
   if (p->band_h != 8) {
     const int rr = 2 * p->r + 1, u = rr >= 5 ? rr : 2 * rr;  // whole turns of the accumulators
-    return (h + 2 * p->r + u - 1) / u * u;
+    return (h + 2 * p->r * T + T - 1 + u - 1) / u * u;
   }
   const int np = p->r + 1, up = np >= 3 ? np : 2 * np;
   return ((h + 1) / 2 + T * p->r + T - 1 + up - 1) / up * up;
@@ -847,6 +848,7 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     g.nblocks = ndim == 1 ? g.nsegs_y : g.nstrips * g.nsegs_y * g.nsegs_z;
     set_batch_geometry(p);
     // two fused steps per launch: 2-D, radius <= 3, a 16-bit carry or paired-line bands
+    const bool wide2 = ndim == 2 && radius > 3 && low && engine == SPIDER_ENGINE_SPARSE && !p->row_swap;
     const bool tb2_ok = (ndim == 2 && radius <= 3 && (low || pair) && !p->row_swap) ||
                         (ndim == 3 && radius == 1 && low);
     // three or four: paired-line bands with a 16-bit carry (the dense engine
@@ -882,12 +884,19 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
         else
           T = pts >= (1LL << 22) && (pts < (1LL << 23) || pts >= (1LL << 24)) ? 4 : T;
       }
+      // Wide stencils: two steps, from the size at which their longer chain (4r + 1 lines of
+      // halo per segment instead of 2r) is made up for: r = 4 and 5 everywhere (512^2 4.5 us
+      // per step against 4.9, 5.5 against 5.8), r = 6 from 2^22 points (2048^2 10.0 against
+      // 10.4, 1024^2 7.3 against 7.2), r = 7 from 2^24 (4096^2 24.6 against 25.0, 2048^2 12.3
+      // against 12.0).  Explicit depths of wide stencils stay at one.
+      if (wide2) T = radius <= 5 || pts >= (radius == 6 ? 1LL << 22 : 1LL << 24) ? 2 : 1;
       p->line_deep = tb1_ok && o.tile_h == 0;
       p->tune_depth = o.autotune && o.tile_h == 0 && p->max_time_block > 2 && !p->line_deep;
     } else {
       T = o.time_block;
     }
-    set_time_block(p, std::min(T, p->max_time_block), o.tile_h);
+    const bool two = wide2 && o.time_block == 0 && T == 2;
+    set_time_block(p, two ? 2 : std::min(T, p->max_time_block), o.tile_h);
   }
   if (o.autotune && o.tile_h == 0 && !p->line_deep && !p->stream) {
     spider_status st = ensure_scratch(p);
