@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -313,13 +314,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((sizeof(T) =
 // CUs) with a halo of S r points on every side (W = tile + 2 S r <= 64 points a
 // side) into LDS once, advances it S steps there (the region still
 // exact after step s shrinks by r per side each step; points outside the grid stay
-// zero), and stores the tile.  In each step a lane owns one column and computes the
-// rows wave, wave + NW, ... of it (NW = 16 waves up to radius 2, 8 at radius 3,
-// whose taps take more registers), every point independently, so the LDS reads of
-// a thread's points overlap: with few tiles per grid the per-step latency, not the
-// arithmetic, sets the time.  Each point sums its taps in the single-step kernel's
-// order (kernel rows, then taps along x, one fused multiply-add each), so the two
-// kernels agree bit for bit.
+// zero), and stores the tile.  In each step a lane owns one column and a wave an
+// equal share of consecutive rows: each row's 2r + 1 values are read from LDS once and
+// go into the sums of all the wave's rows they touch, (1 + 2 r / rows) (2r + 1) reads a
+// point instead of the (2r + 1)^2 that a point by itself needs and that bound the step.
+// A tile's step is then its instructions: LDS rows are 64 points long whatever the tile,
+// so every address but a wave's first is a constant, and no store needs a branch.  Fifty
+// steps, us, before and now: fp64 r = 1 256^2 58 and 47, fp32 r = 3 512^2 177 and 117, fp64
+// r = 3 1024^2 923 and 535.  16 waves up to radius 2, 8 at radius 3 (fp32 r = 3 1024^2: 299
+// at 8, 396 at 16, whose rows are read by more waves).  Each point sums its taps in the
+// single-step kernel's order (kernel rows, then taps along x, one fused multiply-add
+// each), so the two kernels agree bit for bit.
 constexpr int kFusedTile = 32;  // the largest tile side; the step limit is set for it
 constexpr int kFusedMaxSide = 64;
 
@@ -336,10 +341,11 @@ __global__ __launch_bounds__(64 * fused_waves<R>()) void direct2d_fused_kernel(
   constexpr int NW = fused_waves<R>();
   extern __shared__ __align__(16) unsigned char fused_lds[];
   const int H = S * R, W = tile + 2 * H;
-  T* const lds = reinterpret_cast<T*>(fused_lds);  // two W x W buffers; indexed by offset so
+  constexpr int kRow = kFusedMaxSide;               // LDS row length: every row offset is a constant
+  T* const lds = reinterpret_cast<T*>(fused_lds);  // two buffers of W rows; indexed by offset so
                                                     // the accesses stay LDS instructions
   const int gx0 = (int)(blockIdx.x % ntx) * tile - H, gy0 = (int)(blockIdx.x / ntx) * tile - H;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   T c[RR * RR];
 #pragma unroll
   for (int i = 0; i < RR * RR; ++i) {
@@ -349,6 +355,7 @@ __global__ __launch_bounds__(64 * fused_waves<R>()) void direct2d_fused_kernel(
   }
   const int x = gx0 + lane;
   const bool xin = x >= 0 && x < nx;
+  const int wl = min(lane, W - 1);
   {
     // every load of the tile issued before the first LDS write (rows wave, wave + NW, ...)
     constexpr int kRowsPerWave = kFusedMaxSide / NW;
@@ -361,78 +368,67 @@ __global__ __launch_bounds__(64 * fused_waves<R>()) void direct2d_fused_kernel(
 #pragma unroll
     for (int k = 0; k < kRowsPerWave; ++k) {
       const int ly = wave + NW * k;
-      if (lane < W && ly < W) lds[ly * W + lane] = ld[k];
+      if (lane < W && ly < W) lds[ly * kRow + lane] = ld[k];
     }
   }
   __syncthreads();
   for (int s = 1; s <= S; ++s) {
-    const T* src = lds + ((s - 1) & 1) * W * W;
-    T* dst = lds + (s & 1) * W * W;
+    const T* src = lds + ((s - 1) & 1) * W * kRow;
+    T* dst = lds + (s & 1) * W * kRow;
     const int lo = s * R, hi = W - s * R;  // rows and columns [lo, hi) are exact after step s
-    // a lane computes column `lane`; LDS reads are issued unconditionally (at
-    // clamped, valid positions) so that they overlap, and only the writes are
-    // predicated
+    // a lane computes column `lane`, at clamped, valid positions outside [lo, hi)
     const int lx = min(max(lane, lo), hi - 1);
-    constexpr int KR = kFusedMaxSide / NW;
-    if constexpr (R == 1) {
-      // radius 1: a wave owns KR consecutive rows and reads the KR + 2 input rows
-      // they need once (3 values per row per lane), all before the first product
-      const int ly0 = lo + KR * wave;
-      T v[KR + 2][3];
+    auto rows = [&](auto kr) {
+      constexpr int KR = kr.value;
+      if (lo + KR * wave >= hi) return;
+      const int ly0 = min(lo + KR * wave, hi - KR);  // (the last wave may repeat rows of the one before)
+      const T* p0 = src + (ly0 - R) * kRow + (lx - R);
+      T* q0 = dst + ly0 * kRow + wl;
+      T acc[KR];
 #pragma unroll
-      for (int j = 0; j < KR + 2; ++j) {
-        const T* p = src + min(ly0 - 1 + j, hi) * W + (lx - 1);
+      for (int k = 0; k < KR; ++k) acc[k] = T(0);
 #pragma unroll
-        for (int t = 0; t < 3; ++t) v[j][t] = p[t];
-      }
+      for (int j = 0; j < KR + 2 * R; ++j) {
+        const T* p = p0 + j * kRow;
+        T v[RR];
 #pragma unroll
-      for (int k = 0; k < KR; ++k) {
-        T acc = T(0);
+        for (int t = 0; t < RR; ++t)
+          if (ZM != 2 || t == R || (j >= R && j < KR + R)) v[t] = p[t];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-#pragma unroll
-          for (int t = 0; t < 3; ++t) {
-            if (ZM == 2 && a != 1 && t != 1) continue;
-            const T cc = c[a * 3 + t];
-            if (ZM != 1 || cc != T(0)) acc = fma_t<T>(cc, v[k + a][t], acc);
-          }
-        }
-        const int ly = ly0 + k;
-        if (ly < hi && lane >= lo && lane < hi) {
-          const int y = gy0 + ly;
-          const bool inside = xin && y >= 0 && y < ny;
-          if (s < S)
-            dst[ly * W + lane] = inside ? acc : T(0);
-          else if (inside)
-            out[(size_t)y * nx + x] = acc;
-        }
-      }
-    } else {
-      // wider stencils: rows lo + wave + NW k, one point at a time (their reads
-      // alone fill the registers)
-#pragma unroll
-      for (int k = 0; k < KR; ++k) {
-        const int ly = lo + wave + NW * k;
-        const T* p = src + (min(ly, hi - 1) - R) * W + (lx - R);
-        T acc = T(0);
-#pragma unroll
-        for (int a = 0; a < RR; ++a) {
+        for (int k = 0; k < KR; ++k) {
+          const int a = j - k;
+          if (a < 0 || a >= RR) continue;
 #pragma unroll
           for (int t = 0; t < RR; ++t) {
             if (ZM == 2 && a != R && t != R) continue;
             const T cc = c[a * RR + t];
-            if (ZM != 1 || cc != T(0)) acc = fma_t<T>(cc, p[a * W + t], acc);
+            if (ZM != 1 || cc != T(0)) acc[k] = fma_t<T>(cc, v[t], acc[k]);
           }
         }
-        if (ly < hi && lane >= lo && lane < hi) {
-          const int y = gy0 + ly;
-          const bool inside = xin && y >= 0 && y < ny;
-          if (s < S)
-            dst[ly * W + lane] = inside ? acc : T(0);
-          else if (inside)
-            out[(size_t)y * nx + x] = acc;
+      }
+      if (s < S) {
+        // (columns outside [lo, hi) are not read again: column W - 1 takes what lies beyond)
+#pragma unroll
+        for (int k = 0; k < KR; ++k) {
+          const int y = gy0 + ly0 + k;
+          q0[k * kRow] = xin && y >= 0 && y < ny ? acc[k] : T(0);
+        }
+      } else if (xin && lane >= lo && lane < hi) {
+#pragma unroll
+        for (int k = 0; k < KR; ++k) {
+          const int y = gy0 + ly0 + k;
+          if (y >= 0 && y < ny) out[(size_t)y * nx + x] = acc[k];
         }
       }
+    };
+    const int share = (hi - lo + NW - 1) / NW;  // rows per wave, 1 .. kFusedMaxSide / NW
+    if (share <= 1) rows(std::integral_constant<int, 1>{});
+    else if (share == 2) rows(std::integral_constant<int, 2>{});
+    else if (share == 3) rows(std::integral_constant<int, 3>{});
+    else if (share == 4) rows(std::integral_constant<int, 4>{});
+    else if constexpr (NW < 16) {
+      if (share <= 6) rows(std::integral_constant<int, 6>{});
+      else rows(std::integral_constant<int, 8>{});
     }
     if (s < S) __syncthreads();
   }
@@ -526,9 +522,9 @@ static hipError_t direct_zm(int zmode, int ndim, int r, const void* in, void* ou
   }
 }
 
-// LDS bytes of the fused 2-D kernel at S steps per launch.
-static size_t direct2d_fused_lds(int r, int elem, int S, int tile = kFusedTile) {
-  const size_t W = (size_t)tile + 2 * (size_t)S * r;
+// Points of the fused 2-D kernel's two tiles at S steps per launch, in bytes.
+static size_t direct2d_fused_lds(int r, int elem, int S) {
+  const size_t W = (size_t)kFusedTile + 2 * (size_t)S * r;
   return 2 * W * W * (size_t)elem;
 }
 
@@ -546,7 +542,7 @@ template <typename T, int ZM>
 static hipError_t direct2d_fused_zm(int r, const void* in, void* out, int ny, int nx, const void* w, int S,
                                     int tile, hipStream_t s) {
   const int ntx = (nx + tile - 1) / tile, nty = (ny + tile - 1) / tile;
-  const size_t lds = direct2d_fused_lds(r, (int)sizeof(T), S, tile);
+  const size_t lds = 2 * (size_t)(tile + 2 * S * r) * kFusedMaxSide * sizeof(T);  // at most 64 KB
   const dim3 grid(ntx * nty);
   const T* pin = static_cast<const T*>(in);
   T* pout = static_cast<T*>(out);
