@@ -106,6 +106,9 @@ static int auto_tile_h_3d(const spider_plan_s* p) {
   return (int)h;
 }
 
+// Time loops of up to this many launches are enqueued launch by launch.
+constexpr int kEagerLaunches = 12;
+
 // Grids from this size on advance several steps per streaming launch.
 constexpr long long kDirectStreamDeepPoints = (1LL << 20) + (1LL << 17);
 
@@ -925,9 +928,10 @@ spider_status spider_apply(spider_plan_t p, const void* in, void* out, int steps
     if (st != SPIDER_OK) return st;
   }
   const LoopShape L = loop_launches(p, steps);
-  // a loop of one launch gains nothing from a graph but the graph's own launch cost,
-  // nor does a line's loop of a few launches, each long enough to cover the next's
-  if (!p->use_graph || steps < 2 || L.total < 2 || (L.deep && L.total <= 8)) return enqueue_steps(p, in, out, steps, s);
+  // a loop of a few launches is through before a graph's own launch cost is made up for:
+  // 512^2 fp16, us, replayed and enqueued, 2 launches 20.7 and 10.5, 6 30.1 and 26.0, 12
+  // 54.6 and 52.5, 24 103.7 and 105.1; fp32 r = 3 direct 27.2 and 22.4, 139.5 and 136.0 at 12
+  if (!p->use_graph || steps < 2 || L.total <= kEagerLaunches) return enqueue_steps(p, in, out, steps, s);
   if (L.total > 2 * kGraphBody) return enqueue_long(p, in, out, L, s);
   // Replay a graph of the whole time loop, captured once per (in, out, steps).
   auto key = std::make_tuple(in, (const void*)out, steps);
