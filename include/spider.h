@@ -73,18 +73,24 @@ typedef struct {
                           bits once per launch instead of once per step (single-step
                           launches are those of split 2); other 16-bit grids: INVALID */
     int tile_h;    /* output rows per wavefront segment, 0 = chosen by the autotuner */
-    int use_graph; /* 1 = capture each (in, out, steps) time loop of two or more launches
-                      once as a hipGraph and replay it (default; a loop of one launch is
-                      launched directly), 0 = launch every step */
+    int use_graph; /* 1 = capture each (in, out, steps) time loop of more than twelve
+                      launches once as a hipGraph and replay it (default; shorter loops
+                      are launched directly), 0 = launch every step */
     int autotune;  /* 1 = when tile_h is 0, time candidate segment heights on the device at
                       plan time and keep the fastest (results cached per shape, radius,
                       engine and dtype for the life of the process); 0 = occupancy heuristic */
     int time_block; /* time steps fused per launch, 0..16 (default 0 = automatic):
                        - paired-line bands with a 16-bit carry: up to four (the dense
-                         engine three); automatic: four from 2^25 points, three from
-                         2^23, else two;
+                         engine three); automatic, sparse engine: r = 1 four from 2^19
+                         points, else two; r = 2 three from 2^23, else two; r = 3 four
+                         from 2^22 (three between 2^23 and 2^24), else two; dense
+                         engine: three from 2^23 points, else two;
                        - paired-line bands with an fp32 carry: up to three on the sparse
-                         engine, two on the dense one; automatic: as above, capped;
+                         engine, two on the dense one; automatic, sparse engine: three
+                         from 2^22 points (r = 2: 2^23), else two;
+                       - 2-D grids of radius 4 to 7, 16-bit carry, sparse engine,
+                         automatic only: two (r = 6 from 2^22 points, r = 7 from 2^24),
+                         with the bits of single steps;
                        - other 2-D grids of radius <= 3 on the matrix engines with a
                          16-bit carry: two;
                        - 1-D lines of radius <= 3 (16-bit or fp32 carry): up to four;
@@ -173,8 +179,8 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
  *   steps    >= 0
  * The plan's scratch buffer holds intermediate steps, so two applies of one plan
  * must not overlap in time (use one plan per concurrent stream).
- * With use_graph, a loop of at most 512 launches is captured once per (in, out,
- * steps) as one graph and replayed; a longer loop replays one cached graph per
+ * With use_graph, a loop of 13 to 512 launches is captured once per (in, out,
+ * steps) as one graph and replayed (a shorter one is launched directly); a longer loop replays one cached graph per
  * 256-launch body (so graphs stay bounded in size) and launches the remainder
  * directly.  The caches hold at most 64 and 16 graphs per plan; evicting one
  * waits for the device first.
@@ -264,10 +270,11 @@ spider_status spider_measure_matrix_rate(int sparse, int waves_per_simd, int ite
  * Runs grids of uneven size and stencil shape together.  Grids whose plan uses a
  * matrix engine with a 16-bit carry, the implicit row swap and a 2-D radius of 1..3
  * or a 3-D radius of 1 are batched, one sequence of launches per (carry dtype,
- * engine): launch k advances every such grid that still has work, 2-D grids with
- * paired-line bands by two fused time steps per launch (steps[i] / 2 launches, then
- * one single step when steps[i] is odd), other grids by one step.  Each of their
- * results equals spider_apply of a plan with time_block = 2 bit for bit (one step
+ * engine, 2-D or 3-D): launch k advances every such grid that still has work, 2-D grids
+ * with paired-line bands by two fused time steps per launch, by four where r is odd and
+ * the engine sparse (then two, then one, for what is left), other grids by one step.
+ * The 2-D and the 3-D sequence do not wait for each other where both are replayed from
+ * one graph.  Each of their results equals spider_apply of a plan with time_block = 2 bit for bit (one step
  * per launch where two cannot be fused; a plan fusing more steps agrees up to
  * rounding).  Every other plan (the direct engine, an fp32 carry, 1-D lines, larger
  * radii, the explicit row swap) runs its own time loop after them on the same
@@ -287,8 +294,8 @@ spider_status spider_apply_batch(int n, const spider_plan_t* plans, const void* 
  * current HIP device.  Requests are admitted while their device footprint
  * (two grid-sized buffers of the plan's carry dtype) fits in `hbm_budget_bytes`
  * and a slot is free (max_slots); admitted requests share every round's
- * batched launch (2-D grids whose plan fuses three or four steps, and plans that
- * batched apply runs alone, run their own launches in the round instead), and a
+ * batched launch (2-D grids of 2^23 points and more whose plan fuses three or four
+ * steps, and plans that batched apply runs alone, run their own launches in the round instead), and a
  * request that arrives while others run joins at the next round.  Grid state
  * stays on the device between rounds.  Any plan spider_apply accepts is accepted.
  */

@@ -1,6 +1,8 @@
 // Device code of the paired-line band (2-D, r <= 3) shared by its kernels and
-// the batched kernel: LDS layout, gather, operand product, stores and the
-// one-step body.  See kernels_band_pair.hip for the scheme.
+// the batched kernel: LDS layout, gather, operand product, stores, the one- and
+// two-step bodies of even radii and the dense engine, and the bodies of odd radii
+// on the sparse engine at any depth (quads, at the end).  See kernels_band_pair.hip
+// for the scheme.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -435,7 +437,9 @@ __device__ __forceinline__ void band2d_pair_tb2_body(const BandGrid& g, int w, u
 // and a lo copy of two lines in K, every line pair is gathered once instead of
 // twice, the operand of pair j (registers of the older pair kept, those of the one
 // before it replaced) is ready before the matrix instructions start, and only
-// (r - 1) / 2 + 1 output pairs per level are in flight instead of r + 1: MEASURED
+// (r - 1) / 2 + 1 output pairs per level are in flight instead of r + 1.  The
+// instructions per output are the same r + 1.  Box-2D49P 10240^2, us per step: fp16,
+// four steps per launch, 39.3 before and 35.4 now; fp32 carry, three, 82.3 and 76.9.
 
 // The coefficient operands: instruction k for operands whose lower half is the older
 // pair (a[0]) or the newer one (a[1]: the same with its K halves exchanged).

@@ -18,6 +18,10 @@
 // LDS as 33 16-byte chunks, each followed by 2 pad dwords; the gather of a lane
 // reads window pairs (g, g + 4) of two 2:4 groups with one ds_read2_b32 each,
 // bank-conflict free, and the second half reads 96 dwords (16 chunks) further.
+//
+// Odd radii on the sparse engine hold four input lines in K instead, one copy each
+// of two pairs, and multiply the hi and the lo coefficients by instructions of their
+// own (band_pair.h, quads): as many instructions, half the gathers.
 #include <hip/hip_runtime.h>
 
 #include "band_pair.h"

@@ -14,7 +14,8 @@
 // Lines enter LDS one input pair at a time, into a two-slot ring, just before
 // the pair is multiplied; the pair's registers are then reloaded with the line
 // one body ahead.  This keeps LDS at 4 line pairs (+ 4 per fused level) per wave.
-// Without the input split the arithmetic is the 16-bit paired kernels': the
+// Odd radii on the sparse engine run quads (band2d_quad_f32_body), as the 16-bit
+// kernels do.  Without the input split the arithmetic is the 16-bit paired kernels': the
 // result rounded to 16 bits equals the 16-bit carry's, bit for bit.
 #include <hip/hip_runtime.h>
 
