@@ -70,5 +70,6 @@ def test_automatic_plans(r, shape, carry):
     for steps in (1, 7):
         y, info = run(w, x, steps, carry=carry, engine="sparse")
         z, other = run(w, x, steps, carry=carry, engine="sparse", time_block=info["time_block"], tile_h=64)
-        assert other["time_block"] == info["time_block"]
+        # (explicit depths of wide stencils stay at one step, with the same bits)
+        assert other["time_block"] == (info["time_block"] if r <= 3 else 1)
         assert torch.equal(y, z), (info["time_block"], steps)
