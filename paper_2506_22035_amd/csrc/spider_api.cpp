@@ -291,8 +291,8 @@ static int band2d_iterations(const spider_plan_s* p, int T, int h) {
 // heights that put k = 1 .. 4 waves on a SIMD the one with the smallest iterations
 // times stretch is taken, and among heights of as many iterations the tallest.
 // Box-2D49P fp16, us per step: 512^2 3.2 at 8 rows (4.8 at 32), 1024^2 3.6 (4.9),
-// 10240^2 35.4 at 232 rows and two waves (40.3 at 468 and one, 38.5 at 156, 40.9 at
-// 224: a few more segments than the chip holds two waves of).  Box-2D9P fp16, 4096^2:
+// 10240^2 35.4 at 228 .. 248 rows and two waves (40.3 at 468 and one, 38.5 at 156, 40.9
+// at 224: a few more segments than the chip holds two waves of).  Box-2D9P fp16, 4096^2:
 // 6.2 at 40 rows and two waves, 6.7 at 72 and one.
 static int model_rows_2d(const spider_plan_s* p, int T, long long nstrips, int max_waves) {
   static const double stretches[2][4] = {{1.0, 1.6, 2.3, 3.0}, {1.0, 1.45, 2.15, 2.85}};
@@ -302,7 +302,9 @@ static int model_rows_2d(const spider_plan_s* p, int T, long long nstrips, int m
   int best = top;
   double best_cost = 1e300;
   for (int k = 1; k <= std::min(4, max_waves); ++k) {
-    const long long segs = std::max<long long>(1, 4LL * k * p->ncu / nstrips);
+    // (a launch that fills the last few slots puts an extra wave on some SIMDs: fp32 carry,
+    // 10240^2, us per step, 2025 waves of 2048 77.1, 1980 waves 73.7 .. 75.2)
+    const long long segs = std::max<long long>(1, 4LL * k * p->ncu * 31 / 32 / nstrips);
     int h = (int)((p->ny + segs - 1) / segs);
     h = std::min((h + unit - 1) / unit * unit, top);
     const int it = band2d_iterations(p, T, h);
