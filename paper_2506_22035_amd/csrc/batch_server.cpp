@@ -265,7 +265,8 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
   }
   P.off[maxl] = bytes;
   P.desc.assign(bytes, 0);
-  std::vector<LaunchPart> parts, last;
+  std::vector<LaunchPart> parts, last;  // of this launch, and of the one whose height is used
+  long long last_depth = 0;
   int height = 0;
   for (int st = 0; st < maxl; ++st) {
     char* base = P.desc.data() + P.off[st];
@@ -279,11 +280,23 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
       const int T = st < n4[i] ? 4 : st < n4[i] + n2[i] ? 2 : 1;
       parts.push_back({p, T == 4 ? &p->grid_batch4 : T == 2 ? &p->grid_batch2 : &p->grid_batch, T});
     }
-    // (the same grids at the same depths as in the launch before have the same height)
-    bool same = parts.size() == last.size();
-    for (size_t i = 0; same && i < parts.size(); ++i) same = parts[i].geom == last[i].geom;
-    if (!same) height = launch_height(parts, ndim);
-    last = parts;
+    // The same grids at the same depths as before have the same height; of many grids, a
+    // few that end or change depth do not matter (the choice looks at every grid for
+    // every candidate, and thousands of grids may end at as many launches).
+    long long depth = 0;
+    for (const auto& u : parts) depth += u.T;
+    bool same;
+    if (parts.size() < 64) {
+      same = parts.size() == last.size();
+      for (size_t i = 0; same && i < parts.size(); ++i) same = parts[i].geom == last[i].geom;
+    } else {
+      same = 8 * parts.size() > 7 * last.size() && 8 * depth > 7 * last_depth && !last.empty();
+    }
+    if (!same) {
+      height = launch_height(parts, ndim);
+      last = parts;
+      last_depth = depth;
+    }
     int j = 0, acc = 0;
     for (int i = 0; i < n; ++i) {
       const BatchItem& it = items[i];
@@ -372,11 +385,11 @@ spider_status enqueue_batch(BatchArena& A, const std::vector<BatchItem>& items, 
     if (st != SPIDER_OK) break;
     at += P.desc.size();
   }
-  if (st != SPIDER_OK) return st;
+  // (also after a failure: launches already enqueued read the descriptors)
   e = hipEventRecord(A.done, s);
-  if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
-  A.pending = true;
-  return SPIDER_OK;
+  if (e == hipSuccess) A.pending = true;
+  if (st != SPIDER_OK) return st;
+  return e == hipSuccess ? SPIDER_OK : hip_fail(e, "hipEventRecord");
 }
 
 // ------------------------------------------------------------------ graph-captured batches

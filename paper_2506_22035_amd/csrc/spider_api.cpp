@@ -928,7 +928,6 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
       spider_plan_destroy(p);
       return st;
     }
-    if (engine != SPIDER_ENGINE_DIRECT) set_batch_geometry(p);  // from the tuned height
   }
   *out = p;
   return SPIDER_OK;
