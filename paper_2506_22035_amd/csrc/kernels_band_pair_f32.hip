@@ -421,7 +421,7 @@ __device__ __forceinline__ void band2d_pair_f32_bodyT(const BandGrid& g, int w, 
 
 // Odd radii on the sparse engine: the stream of band2d_quad_body (band_pair.h) with
 // every line as a hi (and, XLO, a lo) 16-bit line and every instruction on the hi
-// and then on the lo quads.  Sums of a level leave as hi / lo lines of the next.
+// and on the lo quads (the small products first, see iter).  Sums of a level leave as hi / lo lines of the next.
 template <int R, int OP, bool ALIGNED, bool XLO, int T, int EDGE>
 __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, uint32_t* lds) {
   constexpr int NS = XLO ? 2 : 1;
@@ -518,16 +518,55 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
         for (int f = 0; f < 2; ++f)
           acc[t][f].s[S] = quad_mma<OP, R, K>(NEW ^ quad_parity<R, T>(t), acc[t][f].s[S], A, bq[t][f][s]);
     };
-    // the instructions that complete a pair: the second quad's (r = 3), or all (r = 1)
-    constexpr int K0 = R == 3 ? 2 : 0;
+    // With the input split, products with a lo part (of a coefficient or an input) are
+    // 2^-11 of the others and less, and every instruction rounds the sum it adds to: they
+    // are summed first, while the sum is small.  With r = 1 nothing is carried from one
+    // iteration to the next, so they get a sum of their own, which one fp32 addition joins
+    // to the others' (as the start of one chain, an instruction cuts them off at its own
+    // larger products, always downwards: 0.1 of a rounding per step, which adds up where
+    // the stencil averages).  With r = 3 they go first on the chain: the registers of
+    // separate sums do not exist (100 B spilled, twice the time).  Error against fp64 of
+    // fp16 operands, without the split's own, in roundings of the result (box, r = 1 and
+    // 3): hi products first 1.83 and 2.46, two lines per instruction 1.79 and 2.32, now
+    // 1.17 and 1.65.  (us per step, hi products first and now: r = 1 4096^2 12.6 and 12.9,
+    // 10240^2 63.1 and 63.7; r = 3 10240^2 73.0 and 73.3.)
+    constexpr int K0 = R == 3 ? 2 : 0;  // the instructions that complete a pair: the second quad's (r = 3), or all (r = 1)
     if constexpr (R == 1) {
+      f32x4 lo[T][2];
 #pragma unroll
-      for (int t = 0; t < T; ++t) acc[t][0].s[0] = acc[t][1].s[0] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) acc[t][f].s[0] = lo[t][f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      if constexpr (XLO) {
+        auto each_lo = [&](auto kc, int s) {
+          constexpr int K = decltype(kc)::value;
+#pragma unroll
+          for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int f = 0; f < 2; ++f)
+              lo[t][f] = quad_mma<OP, R, K>(NEW ^ quad_parity<R, T>(t), lo[t][f], A, bq[t][f][s]);
+        };
+        each_lo(std::integral_constant<int, 1>{}, NS - 1);
+        each_lo(std::integral_constant<int, 1>{}, 0);
+        each_lo(std::integral_constant<int, 0>{}, NS - 1);
+      }
+      each(std::integral_constant<int, 0>{}, 0);
+      if constexpr (!XLO) each(std::integral_constant<int, 1>{}, 0);
+      if constexpr (XLO) {
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+          for (int f = 0; f < 2; ++f) acc[t][f].s[0] = acc[t][f].s[0] + lo[t][f];
+      }
+    } else if constexpr (XLO) {
+      each(std::integral_constant<int, K0 + 1>{}, NS - 1);
+      each(std::integral_constant<int, K0>{}, NS - 1);
+      each(std::integral_constant<int, K0 + 1>{}, 0);
+      each(std::integral_constant<int, K0>{}, 0);
+    } else {
+      each(std::integral_constant<int, K0>{}, 0);
+      each(std::integral_constant<int, K0 + 1>{}, 0);
     }
-    each(std::integral_constant<int, K0>{}, 0);
-    if constexpr (XLO) each(std::integral_constant<int, K0>{}, NS - 1);
-    each(std::integral_constant<int, K0 + 1>{}, 0);
-    if constexpr (XLO) each(std::integral_constant<int, K0 + 1>{}, NS - 1);
     // level t's finished pair: the output, or zeroed outside the grid and split for
     // the next level
     const __amdgpu_buffer_rsrc_t rs = pout.next();
@@ -566,10 +605,15 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
       for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int f = 0; f < 2; ++f)
-          acc[t][f].s[S] = quad_mma<OP, R, 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A, bq[t][f][0]);
-      if constexpr (XLO) each(std::integral_constant<int, 0>{}, NS - 1);
-      each(std::integral_constant<int, 1>{}, 0);
-      if constexpr (XLO) each(std::integral_constant<int, 1>{}, NS - 1);
+          acc[t][f].s[S] = quad_mma<OP, R, XLO ? 1 : 0>(NEW ^ quad_parity<R, T>(t), (f32x4){0.f, 0.f, 0.f, 0.f}, A,
+                                                        bq[t][f][NS - 1]);
+      if constexpr (XLO) {
+        each(std::integral_constant<int, 0>{}, NS - 1);
+        each(std::integral_constant<int, 1>{}, 0);
+        each(std::integral_constant<int, 0>{}, 0);
+      } else {
+        each(std::integral_constant<int, 1>{}, 0);
+      }
     }
     // each level's lines of the next iteration replace the older pair of its operands
 #pragma unroll
