@@ -39,6 +39,10 @@ struct spider_plan_s {
   void* d_apack = nullptr;
   void* d_ipack = nullptr;
   void* d_dpack = nullptr;
+  // paired bands, odd radii, sparse engine: operands of the launches that run quads (where
+  // single-step launches do not, behind theirs in d_apack and d_ipack), else null
+  const uint4* quad_apack = nullptr;
+  const uint32_t* quad_ipack = nullptr;
   void* d_coeffs = nullptr;
   void* d_scratch = nullptr;
   size_t grid_bytes = 0;

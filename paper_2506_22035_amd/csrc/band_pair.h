@@ -491,15 +491,15 @@ struct QuadAcc {
   __device__ __forceinline__ void zero() { s[0] = s[R == 3 ? 1 : 0] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
 };
 
-// T = 1 .. 4 steps per launch.  The stream of band2d_pair_tbt_body (kernels_band_pair.hip)
+// T = 2 .. 4 steps per launch.  The stream of band2d_pair_tbt_body (kernels_band_pair.hip)
 // with quads: level t (0 = input, T = output) has its line pairs start at row y0 -
 // (T - t) r; at stream iteration P pass t multiplies the level-t pair P - t (r + 1),
 // staged (t = 0) or written by pass t - 1 in iteration P - 1.  An iteration completes
 // its output pairs first, writes them, and only then starts the next ones (r = 3),
 // gathering the next iteration's lines between those instructions: the LDS round
-// trip is covered by matrix work, and one pair per level is all the LDS holds.  A launch of one step
-// has no level between and stores the 256 columns it computes; T >= 2 steps store
-// pair_tb_width (240 at T = 2).
+// trip is covered by matrix work, and one pair per level is all the LDS holds.  T >= 2
+// steps store pair_tb_width columns (240 at T = 2).  A launch of one step (fp32 carry, split 3) has
+// no level between and stores the 256 columns it computes.
 constexpr int quad_width(int T, int R) {
   return T == 1 ? kStripWPair : T == 2 ? kStripWPair2 : pair_tb_width(T, R);
 }
@@ -736,10 +736,15 @@ __device__ __forceinline__ void quad_bodies(const BandGrid& g, int w, uint32_t* 
     band2d_quad_body<R, OP, true, T, 2>(g, w, lds);
 }
 
-// The body of a paired-band step (T = 1) or of T fused ones for radius R.
-template <int R, int ENG>
+// Whether a launch of T steps at radius R runs quads.  A single step gains nothing from
+// them: it waits for memory, and the paired body loads and multiplies 2 (r + 1) lines
+// between two waits for LDS where quads take two (fp16, us per step, quads and pairs:
+// r = 3 3000 x 3008 11.4 and 9.0, 4096^2 20.0 and 17.8, r = 1 10.8 and 9.7).  Only the
+// fp32 carry's input split keeps them, whose sums they round less often (see
+// band2d_quad_f32_body; 19.2 and 19.2 on 3000 x 3008, r = 3).
+template <int R, int ENG, int T, bool XLO = false>
 constexpr bool use_quad() {
-  return ENG == 1 && R != 2;
+  return ENG == 1 && R != 2 && (T > 1 || XLO);
 }
 
 }  // namespace spider_impl

@@ -1224,7 +1224,7 @@ int band2d_blocks_per_cu(int r, int operand, int engine, bool aligned) {
 // A paired-band unit of T = 1, 2 or 4 steps.
 template <int R, int OP, int ENG, bool AL_ONLY, int T>
 __device__ __forceinline__ void batch_pair(const BandGrid& g, int w, uint32_t* lds, bool al) {
-  if constexpr (use_quad<R, ENG>()) {
+  if constexpr (use_quad<R, ENG, T>()) {
     quad_bodies<R, OP, AL_ONLY, T>(g, w, lds);
   } else if constexpr (T == 2) {
     if (al) band2d_pair_tb2_body<R, OP, ENG, true, true>(g, w, lds);

@@ -19,7 +19,7 @@
 // reads window pairs (g, g + 4) of two 2:4 groups with one ds_read2_b32 each,
 // bank-conflict free, and the second half reads 96 dwords (16 chunks) further.
 //
-// Odd radii on the sparse engine hold four input lines in K instead, one copy each
+// Fused steps of odd radii on the sparse engine hold four input lines in K instead, one copy each
 // of two pairs, and multiply the hi and the lo coefficients by instructions of their
 // own (band_pair.h, quads): as many instructions, half the gathers.
 #include <hip/hip_runtime.h>
@@ -34,20 +34,12 @@ template <int R, int OP, int ENG, bool ALIGNED>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ALIGNED ? 4 : (ENG == 1 ? 3 : 2)))) void band2d_pair_kernel(BandGrid g) {
   constexpr int NP = R + 1;
   constexpr int UP = (NP >= 3) ? NP : 2 * NP;
-  __shared__ uint32_t lds[use_quad<R, ENG>() ? quad_lds_dw<1>() : 2 * UP * kPairRowDw];
+  __shared__ uint32_t lds[2 * UP * kPairRowDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  const bool inside = ALIGNED || pair_inside(g, w, kStripWPair, kPairWinLead);
-  if constexpr (use_quad<R, ENG>()) {
-    if (inside)
-      band2d_quad_body<R, OP, true, 1, 0>(g, w, lds);
-    else
-      band2d_quad_body<R, OP, ALIGNED, 1, 2>(g, w, lds);
-  } else {
-    if (inside)
-      band2d_pair_body<R, OP, ENG, true>(g, w, lds);
-    else
-      band2d_pair_body<R, OP, ENG, ALIGNED>(g, w, lds);
-  }
+  if (ALIGNED || pair_inside(g, w, kStripWPair, kPairWinLead))
+    band2d_pair_body<R, OP, ENG, true>(g, w, lds);
+  else
+    band2d_pair_body<R, OP, ENG, ALIGNED>(g, w, lds);
 }
 
 // ----------------------------------------------------------------------------- two fused steps
@@ -57,9 +49,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ENG == 1 ? 3
     BandGrid g) {
   constexpr int NP = R + 1;
   constexpr int UP = (NP >= 3) ? NP : 2 * NP;
-  __shared__ uint32_t lds[use_quad<R, ENG>() ? quad_lds_dw<2>() : (2 * UP + 4) * kPairRowDw];
+  __shared__ uint32_t lds[use_quad<R, ENG, 2>() ? quad_lds_dw<2>() : (2 * UP + 4) * kPairRowDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  if constexpr (use_quad<R, ENG>()) {
+  if constexpr (use_quad<R, ENG, 2>()) {
     quad_bodies<R, OP, ALIGNED, 2>(g, w, lds);
     return;
   }
@@ -69,11 +61,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ENG == 1 ? 3
     const int xp = strip * kStripWPair2 - kPairWinLead;
     const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
     if (xp >= 0 && xp + (ALIGNED ? 256 : 260) <= g.nx && y0 - 2 * R >= 0 && y0 + hrows + 2 * R + 2 <= g.ny) {
-      if constexpr (!use_quad<R, ENG>()) band2d_pair_tb2_body<R, OP, ENG, true, false>(g, w, lds);
+      if constexpr (!use_quad<R, ENG, 2>()) band2d_pair_tb2_body<R, OP, ENG, true, false>(g, w, lds);
       return;
     }
   }
-  if constexpr (!use_quad<R, ENG>()) band2d_pair_tb2_body<R, OP, ENG, ALIGNED, true>(g, w, lds);
+  if constexpr (!use_quad<R, ENG, 2>()) band2d_pair_tb2_body<R, OP, ENG, ALIGNED, true>(g, w, lds);
 }
 
 // ----------------------------------------------------------------------------- T fused steps
@@ -269,9 +261,9 @@ template <int R, int OP, int ENG, bool ALIGNED, int T>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void band2d_pair_tbt_kernel(BandGrid g) {
   constexpr int NP = R + 1;
   constexpr int UP = (NP >= 3) ? NP : 2 * NP;
-  __shared__ uint32_t lds[use_quad<R, ENG>() ? quad_lds_dw<T>() : (2 * UP + 4 * (T - 1)) * kPairRowDw];
+  __shared__ uint32_t lds[use_quad<R, ENG, T>() ? quad_lds_dw<T>() : (2 * UP + 4 * (T - 1)) * kPairRowDw];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  if constexpr (use_quad<R, ENG>()) {
+  if constexpr (use_quad<R, ENG, T>()) {
     quad_bodies<R, OP, ALIGNED, T>(g, w, lds);
     return;
   }
@@ -284,12 +276,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ba
   (void)interior;
   if constexpr (ENG == 1) {
     if (interior) {
-      if constexpr (!use_quad<R, ENG>()) band2d_pair_tbt_body<R, OP, ENG, true, T, false>(g, w, lds);
+      if constexpr (!use_quad<R, ENG, T>()) band2d_pair_tbt_body<R, OP, ENG, true, T, false>(g, w, lds);
       return;
     }
   }
   // (the dense engine keeps one body: its second copy would spill)
-  if constexpr (!use_quad<R, ENG>()) band2d_pair_tbt_body<R, OP, ENG, ALIGNED, T, true>(g, w, lds);
+  if constexpr (!use_quad<R, ENG, T>()) band2d_pair_tbt_body<R, OP, ENG, ALIGNED, T, true>(g, w, lds);
 }
 
 namespace {

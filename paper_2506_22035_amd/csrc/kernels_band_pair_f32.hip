@@ -471,7 +471,10 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
 
   LineWalk lin(g.in, y0 - T * R, max(0, y0 - T * R), min(ny, y0 + hrows + T * R), nx * 4);
   PairWalk pout(g.out, y0 - 2 * ((T - 1) * (R + 1) + R), ys, y0 + hrows, nx * 4);
-  PairF32Line stg[2][2];
+  // input pairs on their way: a launch of one step waits for memory, and its registers hold
+  // four (r = 3, us per step, two and four: 3000^2 19.9 and 19.2, 6000 x 6001 65.2 and 61.6)
+  constexpr int D = T == 1 ? 4 : 2;
+  PairF32Line stg[D][2];
   auto load = [&](PairF32Line* v) {
     v[0] = load_pair_f32(lin.next(), mvoff, tvoff);
     v[1] = load_pair_f32(lin.next(), mvoff, tvoff);
@@ -480,8 +483,8 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
     stage_pair_f32<OP, XLO>(d, d + 2 * LINE, lane, mw, tw, v[0]);
     stage_pair_f32<OP, XLO>(d + LINE, d + 3 * LINE, lane, mw, tw, v[1]);
   };
-  load(stg[0]);
-  load(stg[1]);
+#pragma unroll
+  for (int i = 0; i < D; ++i) load(stg[i]);
   stage(lds, stg[0]);
   load(stg[0]);
   QuadAcc<R> acc[T][2];
@@ -508,8 +511,9 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
     gather(t, 1, 0);
   }
 
-  auto iter = [&](int P, auto nc) {
-    constexpr int NEW = decltype(nc)::value, S = R == 3 ? 1 - NEW : 0;  // P % 2; the place of the pairs completed now
+  auto iter = [&](int P, auto pc) {  // pc: P % D
+    constexpr int Q1 = (decltype(pc)::value + 1) % D;  // the place of input pair P + 1
+    constexpr int NEW = decltype(pc)::value % 2, S = R == 3 ? 1 - NEW : 0;  // P % 2; the place of the pairs completed now
     auto each = [&](auto kc, int s) {
       constexpr int K = decltype(kc)::value;
 #pragma unroll
@@ -597,8 +601,8 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
     for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int f = 0; f < 2; ++f) emit(t, f, acc[t][f].s[S]);
-    stage(lds, stg[1 - NEW]);  // input pair P + 1
-    load(stg[1 - NEW]);        // input pair P + 3
+    stage(lds, stg[Q1]);  // input pair P + 1
+    load(stg[Q1]);        // input pair P + 1 + D
     wave_lds_sync();           // the pairs written are visible
     if constexpr (R == 3) {
 #pragma unroll
@@ -632,17 +636,21 @@ __device__ __forceinline__ void band2d_quad_f32_body(const BandGrid& g, int w, u
     }
     wave_lds_sync();
   };
-  for (int P = 0; P < nit; P += 2) {
+  for (int P = 0; P < nit; P += D) {
     iter(P, std::integral_constant<int, 0>{});
     iter(P + 1, std::integral_constant<int, 1>{});
+    if constexpr (D == 4) {
+      iter(P + 2, std::integral_constant<int, 2>{});
+      iter(P + 3, std::integral_constant<int, 3>{});
+    }
   }
 }
 
 template <int R, int OP, int ENG, bool ALIGNED, bool XLO, int T>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((ENG == 1 && T == 1) ? (ALIGNED ? 4 : 3) : 2)))
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((ENG == 1 && T == 1) ? (ALIGNED && !(XLO && R == 3) ? 4 : 3) : 2)))
 void band2d_pair_f32_kernel(BandGrid g) {
   constexpr int PAIRSZ = 2 * (XLO ? 2 : 1) * kPairRowDw;
-  __shared__ uint32_t lds[(use_quad<R, ENG>() ? T : 2 * T) * PAIRSZ];
+  __shared__ uint32_t lds[(use_quad<R, ENG, T, XLO>() ? T : 2 * T) * PAIRSZ];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
   // interior waves (every staged column and rows [y0 - T r, y0 + hrows + T r + 2) inside
   // the grid) skip the zeroing of intermediate values outside it; only the waves at
@@ -652,7 +660,7 @@ void band2d_pair_f32_kernel(BandGrid g) {
   const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
   const bool inside_x = ALIGNED || xp + 260 <= g.nx;
   const bool interior = xp >= 0 && xp + 256 <= g.nx && y0 - T * R >= 0 && y0 + hrows + T * R + 2 <= g.ny;
-  if constexpr (use_quad<R, ENG>()) {
+  if constexpr (use_quad<R, ENG, T, XLO>()) {
     const int edge = quad_edge<R, T>(g, w, true);
     if (!inside_x)
       band2d_quad_f32_body<R, OP, ALIGNED, XLO, T, 2>(g, w, lds);

@@ -235,16 +235,23 @@ spider_status launch_step2(spider_plan_s* p, const void* src, void* dst, hipStre
   return SPIDER_OK;
 }
 
-// Work units inside a batched launch: the plan's one-step segments, but at least
-// 64 lines (2-D) or 16 planes (3-D) tall, since the other grids of the batch help
-// fill the device and taller units amortise their prologue and halo.  1-D plans
-// are not batched.
+// The operands of a launch of several steps.
+static void fused_operands(const spider_plan_s* p, BandGrid* g) {
+  if (!p->quad_apack) return;
+  g->apack = p->quad_apack;
+  g->ipack = p->quad_ipack;
+}
+
+// What a batched launch takes from the plan; it chooses the heights of its segments
+// itself.  1-D plans are not batched.
 void set_batch_geometry(spider_plan_s* p) {
   p->grid_batch = p->grid_template;
   p->batch_fuse = 1;
   if (p->ndim != 2 || p->band_h != 8 || p->carry != p->operand || p->r > 3 || p->row_swap) return;
   p->batch_fuse = p->engine == SPIDER_ENGINE_SPARSE && p->r != 2 ? 4 : 2;
   p->grid_batch2 = p->grid_batch4 = p->grid_template;
+  fused_operands(p, &p->grid_batch2);
+  fused_operands(p, &p->grid_batch4);
   p->grid_batch2.nstrips = (p->nx + kStripW2_host - 1) / kStripW2_host;
   p->grid_batch4.nstrips = (p->nx + pair_tb_width(4, p->r) - 1) / pair_tb_width(4, p->r);
 }
@@ -378,6 +385,7 @@ static int auto_tile_h_tb2(const spider_plan_s* p) {
 static void set_fused_grid(spider_plan_s* p, int tile_h) {
   const int T = p->time_block;
   p->grid_tb2 = p->grid_template;
+  fused_operands(p, &p->grid_tb2);
   if (p->ndim != 1) {
     const int sw = T == 2 ? kStripW2_host : pair_tb_width(T, p->r);
     p->grid_tb2.nstrips = (p->nx + sw - 1) / sw;
@@ -807,33 +815,39 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     p->auto_rows = ndim == 2 && o.time_block == 0 && o.tile_h == 0 && !o.row_swap;
     const int nrows = pair ? radius + 1 : (ndim == 1 ? 1 : (ndim == 2 ? kw : kw * kw));
     p->nrows = nrows;
-    std::vector<PackedRow> rows(nrows);
-    std::vector<uint32_t> ipack(((nrows + 1) / 2) * 64, 0u);
+    // odd radii on the sparse engine: launches of several steps take four input lines per
+    // instruction, as do single steps of the fp32 carry's input split
+    const bool quad = pair && radius != 2 && engine == SPIDER_ENGINE_SPARSE;
+    const bool quad1 = quad && !low && p->split == 3;
+    const int npacked = quad && !quad1 ? 2 * nrows : nrows;  // single-step operands, then the others
+    const int quad_from = quad1 ? 0 : nrows;
+    std::vector<PackedRow> rows(npacked);
+    std::vector<uint32_t> ipack(((npacked + 1) / 2) * 64, 0u);
     std::vector<uint32_t> dpack((size_t)nrows * 64 * 8, 0u);
     uint32_t mask = 0;
-    for (int i = 0; i < nrows; ++i) {
-      const double* row = p->coeffs.data() + (size_t)i * kw;
+    for (int i = 0; i < npacked; ++i) {
+      const int k = i % nrows;
+      const double* row = p->coeffs.data() + (size_t)k * kw;
       bool nz = pair;
       for (int t = 0; t < kw && !pair; ++t) nz |= row[t] != 0.0;
-      if (nz) mask |= 1u << i;
+      if (nz) mask |= 1u << k;
       std::string err;
-      // (odd radii on the sparse engine: four input lines per instruction)
-      const bool quad = pair && radius != 2 && engine == SPIDER_ENGINE_SPARSE;
-      const bool ok = quad ? pack_quad(p->coeffs.data(), radius, p->operand, std::min(p->split, 2), i, &rows[i], &err)
-                    : pair ? pack_pair(p->coeffs.data(), radius, p->operand, std::min(p->split, 2), i, &rows[i], &err)
-                           : pack_row(row, radius, p->operand, std::min(p->split, 2), &rows[i], &err);
+      const int sp = std::min(p->split, 2);
+      const bool ok = quad && i >= quad_from ? pack_quad(p->coeffs.data(), radius, p->operand, sp, k, &rows[i], &err)
+                      : pair                 ? pack_pair(p->coeffs.data(), radius, p->operand, sp, k, &rows[i], &err)
+                                             : pack_row(row, radius, p->operand, sp, &rows[i], &err);
       if (!ok) {
         spider_plan_destroy(p);
         return fail(SPIDER_ERR_INVALID, "%s", err.c_str());
       }
       for (int lane = 0; lane < 64; ++lane) {
         ipack[(i / 2) * 64 + lane] |= (uint32_t)rows[i].idx[lane] << (16 * (i % 2));
-        std::memcpy(&dpack[((size_t)i * 64 + lane) * 8], &rows[i].dense[lane * 16], 32);
+        if (i < nrows) std::memcpy(&dpack[((size_t)i * 64 + lane) * 8], &rows[i].dense[lane * 16], 32);
       }
     }
     p->rowmask = mask;
-    std::vector<uint16_t> apack((size_t)nrows * 64 * 8);
-    for (int i = 0; i < nrows; ++i) std::memcpy(&apack[(size_t)i * 64 * 8], rows[i].a, sizeof(rows[i].a));
+    std::vector<uint16_t> apack((size_t)npacked * 64 * 8);
+    for (int i = 0; i < npacked; ++i) std::memcpy(&apack[(size_t)i * 64 * 8], rows[i].a, sizeof(rows[i].a));
     e = hipMalloc(&p->d_apack, apack.size() * 2);
     if (e == hipSuccess) e = hipMemcpy(p->d_apack, apack.data(), apack.size() * 2, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&p->d_ipack, ipack.size() * 4);
@@ -843,6 +857,10 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     if (e != hipSuccess) {
       spider_plan_destroy(p);
       return hip_fail(e, "operand upload");
+    }
+    if (quad) {  // (nrows is even: two rows of indices share a word)
+      p->quad_apack = static_cast<const uint4*>(p->d_apack) + (size_t)quad_from * 64;
+      p->quad_ipack = static_cast<const uint32_t*>(p->d_ipack) + (quad_from / 2) * 64;
     }
     p->tile_h = o.tile_h ? o.tile_h : (ndim == 1 ? auto_tile_h_1d(p) : ndim == 2 ? auto_tile_h_2d(p) : auto_tile_h_3d(p));
     if (pair) p->tile_h = std::min(p->tile_h + (p->tile_h & 1), p->ny + (p->ny & 1));  // pairs start on even rows
@@ -1016,7 +1034,7 @@ spider_status spider_plan_info(spider_plan_t p, int* engine, int* carry, int* ti
 // mfma), twice over for an fp32 carry split into three terms (hi and lo lines).
 static uint64_t pair_launch_instructions(const spider_plan_s* p, const BandGrid& g, int T) {
   const int np = p->r + 1, up = np >= 3 ? np : 2 * np;
-  const bool quad = p->r != 2 && p->engine == SPIDER_ENGINE_SPARSE;
+  const bool quad = p->quad_apack && g.apack == p->quad_apack;
   uint64_t iters = 0;
   for (int s = 0; s < g.nsegs_y; ++s) {
     const int hrows = std::min(g.seg_h, g.ny - s * g.seg_h);
