@@ -218,8 +218,13 @@ spider_status spider_plan_destroy(spider_plan_t plan);
  *   per input line pair), scratch_bytes (size of the grid-sized scratch buffer the
  *   plan allocates on first use), time_block (steps fused per launch), tile_h2
  *   (segment height of the fused kernel, 0 if time_block is 1 and for the direct
- *   engine, whose fused kernel uses fixed 32 x 32 tiles), band_height (output
- *   points per band row: 16, or 8 for paired-line bands; 0 for the direct engine).
+ *   engine's LDS tiles), band_height (output points per band row: 16, or 8 for
+ *   paired-line bands; 0 for the direct engine).
+ *   Direct plans that stream lines through registers: rows per wave of a launch of one
+ *   step and of time_block steps.  1-D lines advanced in LDS: blocks of 256 points per
+ *   section of a launch of one step and of the deepest launch (time_block is what
+ *   the launches' steps are a multiple of, up to their remainder, and where split 3
+ *   rounds a 16-bit grid).
  *   Any output pointer may be NULL.
  */
 spider_status spider_plan_info(spider_plan_t plan, int* engine, int* carry, int* tile_h,

@@ -278,9 +278,8 @@ int direct2d_stream_max_steps(int r, int dtype, int zero_taps, long long points)
 // Rows per wave.  With k waves per SIMD a launch takes about k (h + 1.2 T r) line
 // times (the levels of the first 2 T r lines start one after the other, so about
 // half of them is spent), and a lone wave or two leave latency uncovered (35 and 10
-// per cent); k is the best of 1 .. 8.  Star r = 3 at T = 4: 8 rows on 1100 x 1003
-// (4.4 us per step; 64 rows 12.5), 24 on 2048^2 (7.1; 64 rows 13.1), 48 on 4096^2
-// (16.3; 128 rows 23.2).
+// per cent); k is the best of 1 .. 8.  Star r = 3, us per step: 2048^2 6.4 at the 19 rows
+// chosen for T = 4 (64 rows 13.1), 4096^2 13.6 at 37 (128 rows 23.2).
 int direct2d_stream_rows(int r, int T, int ny, int nx, int ncu) {
   const long long nstrips = (nx + stream_width(T, r) - 1) / stream_width(T, r);
   int best = ny;

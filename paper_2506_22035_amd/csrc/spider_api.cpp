@@ -454,6 +454,11 @@ struct LoopShape {
   int run_end(int k) const { return k <= fused ? fused : (k <= fused + two ? fused + two : total); }
 };
 
+// Most steps of a line's launch.
+static int line_max_steps(const spider_plan_s* p) {
+  return (p->r == 1 ? kLineDeepMaxSteps : 48) / p->time_block * p->time_block;
+}
+
 static LoopShape loop_launches(const spider_plan_s* p, int steps) {
   LoopShape L;
   const int tb = p->time_block;
@@ -461,10 +466,10 @@ static LoopShape loop_launches(const spider_plan_s* p, int steps) {
     // the fewest launches, of equal depth: a launch's load, store and tail cost about
     // as much as five steps of a long line; a section of 1024 points loses 2 T r of
     // them to its halo (T = 64 at r = 1: 13 %, T = 48 at r = 3: 28 %)
-    const int max_t = p->r == 1 ? kLineDeepMaxSteps : 48;
+    const int max_t = line_max_steps(p);
     const int n = std::max(1, (steps + max_t - 1) / max_t);
     const int per = (steps + n - 1) / n;
-    L.deep = std::max(tb, std::min(max_t / tb * tb, (per + tb - 1) / tb * tb));
+    L.deep = std::max(tb, std::min(max_t, (per + tb - 1) / tb * tb));
     L.fused = steps / L.deep;
     L.rem = steps - L.deep * L.fused;
     L.two = L.rem > 0 ? 1 : 0;
@@ -1011,7 +1016,15 @@ spider_status spider_plan_info(spider_plan_t p, int* engine, int* carry, int* ti
   if (band_height) *band_height = p->engine == SPIDER_ENGINE_DIRECT ? 0 : p->band_h;
   if (engine) *engine = p->engine;
   if (carry) *carry = p->carry;
-  if (tile_h) *tile_h = p->tile_h;
+  int h = p->tile_h, h2 = p->time_block >= 2 && p->engine != SPIDER_ENGINE_DIRECT ? p->tile_h2 : 0;
+  if (p->stream) {
+    h = p->stream_h[0];
+    h2 = p->time_block >= 2 ? p->stream_h[__builtin_ctz((unsigned)p->time_block)] : 0;
+  } else if (p->line_deep) {
+    h = line_deep_choice(p->nx, p->r, 1, p->ncu).nb;
+    h2 = line_deep_choice(p->nx, p->r, line_max_steps(p), p->ncu).nb;
+  }
+  if (tile_h) *tile_h = h;
   if (nrows_nonzero) {
     int n = 0;
     if (p->engine == SPIDER_ENGINE_DIRECT) {
@@ -1023,7 +1036,7 @@ spider_status spider_plan_info(spider_plan_t p, int* engine, int* carry, int* ti
   }
   if (scratch_bytes) *scratch_bytes = p->grid_bytes;
   if (time_block) *time_block = p->time_block;
-  if (tile_h2) *tile_h2 = p->time_block >= 2 && p->engine != SPIDER_ENGINE_DIRECT ? p->tile_h2 : 0;
+  if (tile_h2) *tile_h2 = h2;
   return SPIDER_OK;
 }
 
