@@ -82,7 +82,7 @@ typedef struct {
     int time_block; /* time steps fused per launch, 0..16 (default 0 = automatic):
                        - paired-line bands with a 16-bit carry: up to four (the dense
                          engine three); automatic, sparse engine: r = 1 four from 2^19
-                         points, else two; r = 2 three from 2^23, else two; r = 3 four
+                         points, else two; r = 2 four above 2^26, three from 2^23, else two; r = 3 four
                          from 2^22 (three between 2^23 and 2^24), else two; dense
                          engine: three from 2^23 points, else two;
                        - paired-line bands with an fp32 carry: up to three on the sparse

@@ -919,10 +919,12 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
       // 2^19 points (1024^2 2.4 us per step against 2.7 at two, 4096^2 6.1 against 7.0 at
       // three), with r = 3 from 2^22 (2048^2 4.8 against 5.2; at 2^23 .. 2^24 three are as
       // fast); four steps round as two launches of two do.  fp32 carry: three from 2^22
-      // points.  r = 2 stops at three (8192^2 22.5 against 24.5 at four).
+      // points.  r = 2: four above 2^26 points (fp16 at three and four: 7000^2 17.9 and 18.6,
+      // 8192^2 23.9 and 23.9, 9500^2 31.4 and 30.7, 10240^2 36.4 and 35.7, 12000 x 12288 50.7
+      // and 48.2).
       if (ndim == 2 && pair && engine == SPIDER_ENGINE_SPARSE) {
         if (radius == 2)
-          T = std::min(T, 3);
+          T = std::min(T, pts > (1LL << 26) ? 4 : 3);
         else if (!low)
           T = pts >= (1LL << 22) ? 3 : T;
         else if (radius == 1)
