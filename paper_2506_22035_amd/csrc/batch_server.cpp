@@ -129,11 +129,12 @@ static void set_height(BandGrid& g, int ndim, int h) {
   g.nblocks = g.nstrips * g.nsegs_y * g.nsegs_z;
 }
 
-// One grid's part of one launch: its geometry and steps.
+// One grid's part of one launch: its geometry and steps, and where its costs are kept.
 struct LaunchPart {
   const spider_plan_s* plan;
   const BandGrid* geom;
   int T;
+  size_t row;
 };
 
 // Time a wave alone on its SIMD takes for a unit of h rows or planes (us).
@@ -153,34 +154,79 @@ static double unit_time(const LaunchPart& u, int h) {
 // have short chains, tall ones compute fewer halo lines twice.  (A round of a dozen
 // requests, sides 512 .. 4096 and 64 .. 256, 1 .. 100 steps: 3508 us at a fixed 64 rows
 // and two steps per launch, both dimensions in one launch; 1231 now.)
-static int launch_height(const std::vector<LaunchPart>& parts, int ndim) {
-  const double simds = 4.0 * device_cus(), share = ndim == 3 ? 0.85 : 0.6, fixed = 2.3;
-  const int first = ndim == 3 ? 1 : 8, step = ndim == 3 ? 3 : 4, top = ndim == 3 ? 64 : 256;
-  int best = first;
-  double best_cost = 1e300;
-  for (int h = first; h <= top; h += step) {
-    double longest = 0, total = 0;
-    long long units = 0;
+//
+// The choice is made on the host before the first launch, for every launch whose grids
+// differ from the one before: a grid's costs at all candidates are worked out once per
+// depth, and from 64 grids on only heights a quarter apart are candidates.  (Host time of
+// a call with small grids, 1 .. 40 steps, us: 200 grids 587 with every candidate worked out
+// for every launch, 396 now; 1000 grids 3015 and 1884; 3000 10178 and 6360.)
+class LaunchHeights {
+ public:
+  // extent: of the tallest (deepest) grid, beyond which heights are alike
+  LaunchHeights(int ndim, size_t grids, int extent) : ndim_(ndim) {
+    const int first = ndim == 3 ? 1 : 8, step = ndim == 3 ? 3 : 4;
+    const int top = ndim == 3 ? std::min(64, extent) : std::min(256, (extent + 3) / 4 * 4);
+    for (int h = first; h < top; h += std::max(step, grids < 64 ? 0 : h / 4 / step * step)) heights_.push_back(h);
+    heights_.push_back(top);
+    costs_.resize(3 * grids * heights_.size());
+  }
+  // `row` of a grid's part: three per grid, one for every depth
+  static size_t row(size_t grid, int T) { return 3 * grid + (T == 4 ? 2 : T - 1); }
+
+  int choose(const std::vector<LaunchPart>& parts) {
+    const double simds = 4.0 * device_cus(), share = ndim_ == 3 ? 0.85 : 0.6, fixed = 2.3;
+    const size_t n = heights_.size();
+    std::vector<Sum> sums(n);
     for (const auto& u : parts) {
-      BandGrid g = *u.geom;
-      set_height(g, ndim, h);
-      const double t = unit_time(u, g.seg_h);
-      longest = std::max(longest, t);
-      total += t * g.nblocks;
-      units += g.nblocks;
+      const Cost* c = costs(u);
+      for (size_t i = 0; i < n; ++i) {
+        sums[i].longest = std::max(sums[i].longest, (double)c[i].time);
+        sums[i].total += (double)c[i].time * c[i].blocks;
+        sums[i].units += c[i].blocks;
+      }
     }
     // (large volumes are bound by memory, where tall segments re-read the fewest planes)
-    if (ndim == 3 && h == top && units >= 2 * simds) return h;
-    double k = total / (simds * longest);
-    if (k <= 4.0) k = std::ceil(k);
-    const double cost = fixed + longest * (1.0 + share * std::max(0.0, k - 1.0));
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = h;
+    if (ndim_ == 3 && sums[n - 1].units >= 2 * simds) return heights_[n - 1];
+    int best = heights_[0];
+    double best_cost = 1e300;
+    for (size_t i = 0; i < n; ++i) {
+      double k = sums[i].total / (simds * sums[i].longest);
+      if (k <= 4.0) k = std::ceil(k);
+      const double cost = fixed + sums[i].longest * (1.0 + share * std::max(0.0, k - 1.0));
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = heights_[i];
+      }
     }
+    return best;
   }
-  return best;
-}
+
+ private:
+  struct Cost {
+    float time = 0;  // of one unit
+    int blocks = 0;  // units; 0: not worked out yet
+  };
+  struct Sum {
+    double longest = 0, total = 0;
+    long long units = 0;
+  };
+  const Cost* costs(const LaunchPart& u) {
+    Cost* c = &costs_[u.row * heights_.size()];
+    if (c[0].blocks == 0) {
+      BandGrid g = *u.geom;
+      for (size_t i = 0; i < heights_.size(); ++i) {
+        set_height(g, ndim_, heights_[i]);
+        c[i].time = (float)unit_time(u, g.seg_h);
+        c[i].blocks = g.nblocks;
+      }
+    }
+    return c;
+  }
+
+  int ndim_;
+  std::vector<int> heights_;
+  std::vector<Cost> costs_;
+};
 
 // A batched time loop of grids of one dimension laid out for the device: the per-launch descriptors
 // (BandGrid[m] | int kinds[m] | int begin[m + 1], 256-byte aligned blocks), the
@@ -265,6 +311,9 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
   }
   P.off[maxl] = bytes;
   P.desc.assign(bytes, 0);
+  int extent = 1;
+  for (const auto& it : items) extent = std::max(extent, ndim == 3 ? it.plan->nz : it.plan->ny);
+  LaunchHeights heights(ndim, n, extent);
   std::vector<LaunchPart> parts, last;  // of this launch, and of the one whose height is used
   long long last_depth = 0;
   int height = 0;
@@ -278,11 +327,12 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
       if (nl[i] <= st) continue;
       const spider_plan_s* p = items[i].plan;
       const int T = st < n4[i] ? 4 : st < n4[i] + n2[i] ? 2 : 1;
-      parts.push_back({p, T == 4 ? &p->grid_batch4 : T == 2 ? &p->grid_batch2 : &p->grid_batch, T});
+      parts.push_back({p, T == 4 ? &p->grid_batch4 : T == 2 ? &p->grid_batch2 : &p->grid_batch, T,
+                       LaunchHeights::row(i, T)});
     }
     // The same grids at the same depths as before have the same height; of many grids, a
-    // few that end or change depth do not matter (the choice looks at every grid for
-    // every candidate, and thousands of grids may end at as many launches).
+    // few that end or change depth do not matter (thousands of grids may end at as many
+    // launches).
     long long depth = 0;
     for (const auto& u : parts) depth += u.T;
     bool same;
@@ -293,7 +343,7 @@ static spider_status build_batch(const std::vector<BatchItem>& items, BatchProgr
       same = 8 * parts.size() > 7 * last.size() && 8 * depth > 7 * last_depth && !last.empty();
     }
     if (!same) {
-      height = launch_height(parts, ndim);
+      height = heights.choose(parts);
       last = parts;
       last_depth = depth;
     }
