@@ -177,6 +177,13 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
  *   in, out  device grids of the plan's shape in the plan's carry dtype; `in` is
  *            never written unless in == out (allowed); steps == 0 copies.
  *   steps    >= 0
+ * Infinities and NaN: the direct engine multiplies the non-zero taps only.  On the
+ * matrix engines a non-finite value, given or from an overflow, makes at least the
+ * points that the stencil reaches from it non-finite, and at most those that single
+ * steps do, which also reach the other points of a band row's chunk (zero taps of its
+ * window times infinity).  Which of the points between are reached depends on the depth
+ * and tiling of the launches; equality of depths bit for bit holds for finite values.
+ * A finite result never depends on it.
  * The plan's scratch buffer holds intermediate steps, so two applies of one plan
  * must not overlap in time (use one plan per concurrent stream).
  * With use_graph, a loop of 13 to 512 launches is captured once per (in, out,

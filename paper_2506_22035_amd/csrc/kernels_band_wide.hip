@@ -15,6 +15,8 @@
 // (five lines, five lines ahead) instead of a whole one, and outputs are stored as they
 // complete.  The sums are those of two launches of one step bit for bit: strips start at
 // x = 8 mod 16 in both, and every line's products are added in the order of the lines.
+// (Of finite values; infinities and NaN of the line between the steps reach the strip from
+// the columns that it computes only, whereas single steps multiply whole chunks.)
 #include <hip/hip_runtime.h>
 
 #include "band_common.h"

@@ -20,7 +20,12 @@
 // A section starts at x = 8 mod 16, so its 16-point chunks are those of the
 // single-step kernel and every value is summed in the same order: the result
 // equals single steps (or, for a 16-bit grid with split 3, launches that round
-// the grid at the same steps) bit for bit.
+// the grid at the same steps) bit for bit, as long as values are finite.  An infinity
+// or NaN spreads over whole chunks in single steps (zero taps of a chunk's window times
+// infinity), up to 24 points per step; a section sees T r + 8 points beyond those it
+// stores, so from further off it takes only what the stencil itself reaches.  (To see
+// all, a section would need 16 points per step on either side: 1280 of the 1024 points of
+// a section of four blocks at 40 steps.)
 //
 // In-place update: the operands of up to four blocks are gathered before the
 // group in front of them is written, so a block's window (8 points beyond either
