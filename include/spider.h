@@ -68,17 +68,20 @@ typedef struct {
                       2 = w_hi + w_lo, each rounded (default),
                       3 = fp32 carry: also splits every input value x = x_hi + x_lo
                           and adds the products with x_lo (two instructions per kernel row);
-                          a 16-bit carry on a 1-D line: the fused launches keep their
-                          intermediate steps as such hi/lo pairs and round the grid to 16
-                          bits once per launch instead of once per step (single-step
-                          launches are those of split 2); other 16-bit grids: INVALID */
+                          a 16-bit carry on a 1-D line: intermediate steps are kept as
+                          such hi/lo pairs, and the grid is rounded to 16 bits every
+                          time_block steps instead of every step (with time_block 1:
+                          split 2); other 16-bit grids: INVALID */
     int tile_h;    /* output rows per wavefront segment, 0 = chosen by the autotuner */
     int use_graph; /* 1 = capture each (in, out, steps) time loop of more than twelve
                       launches once as a hipGraph and replay it (default; shorter loops
                       are launched directly), 0 = launch every step */
     int autotune;  /* 1 = when tile_h is 0, time candidate segment heights on the device at
                       plan time and keep the fastest (results cached per shape, radius,
-                      engine and dtype for the life of the process); 0 = occupancy heuristic */
+                      engine and dtype for the life of the process); 0 = a model of the
+                      launch.  No effect on automatic 1-D lines of radius <= 3 and on
+                      direct grids that stream lines (see time_block), which always
+                      take the model's */
     int time_block; /* time steps fused per launch, 0..16 (default 0 = automatic):
                        - paired-line bands with a 16-bit carry: up to four (the dense
                          engine three); automatic, sparse engine: r = 1 four from 2^19
@@ -96,7 +99,7 @@ typedef struct {
                        - 1-D lines of radius <= 3 (16-bit or fp32 carry): up to four;
                          automatic (and tile_h 0): four from 2^22 points, else two, and
                          the launches advance up to 64 steps each in LDS, with the bits
-                         of launches of that many steps;
+                         of launches of four (two) steps;
                        - 3-D grids: two for radius 1 with a 16-bit carry, only when asked
                          for (measured slower on the 512^3 and 256^3 workloads);
                        - the direct engine on 2-D grids of radius <= 3: up to 16 steps
@@ -104,17 +107,18 @@ typedef struct {
                          most 64 points a side (radius 2: 8, radius 3: 5); automatic: the
                          most it allows on grids of up to 2^20 points (where single-step
                          launches are bound by latency); larger grids, automatic (and
-                         tile_h 0), without zero taps inside a box: up to eight steps
-                         (radius 1 in fp32; four or two elsewhere, one for the 49-point
-                         box) streamed through registers; else one; bit-identical to
-                         single steps;
+                         tile_h 0), without zero taps inside a box: streamed through
+                         registers, from 2^20 + 2^17 points up to eight steps (radius 1 in
+                         fp32; four or two elsewhere, one for the 49-point box), below
+                         that one; else one; bit-identical to single steps;
                        - anything else: one.
                        Larger values are capped at the plan's maximum.  With 0 and
                        autotune the matrix-engine plans also time the depths and keep
                        the fastest per step.  A time loop of n steps runs n / T fused
                        launches, then (T > 2) one two-step launch for a remainder of two
                        or three steps, then a single step for one; the direct engine
-                       runs its remainder as one launch.  The results agree to rounding;
+                       runs its remainder as one launch (streamed: one for each power of
+                       two in it).  The results agree to rounding;
                        on 1-D lines and on the direct engine they are identical bit for
                        bit, and see band_height for 2-D. */
     int operand;   /* matrix engines with an fp32 carry: 16-bit operand type, SPIDER_F16
@@ -187,8 +191,8 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
  * The plan's scratch buffer holds intermediate steps, so two applies of one plan
  * must not overlap in time (use one plan per concurrent stream).
  * With use_graph, a loop of 13 to 512 launches is captured once per (in, out,
- * steps) as one graph and replayed (a shorter one is launched directly); a longer loop replays one cached graph per
- * 256-launch body (so graphs stay bounded in size) and launches the remainder
+ * steps) as one graph and replayed (a shorter one is launched directly); a longer
+ * loop replays one cached graph per 256-launch body (so graphs stay bounded in size) and launches the remainder
  * directly.  The caches hold at most 64 and 16 graphs per plan; evicting one
  * waits for the device first.
  * Errors: INVALID (null plan/pointer, steps < 0, or a device other than the one
@@ -286,8 +290,8 @@ spider_status spider_measure_matrix_rate(int sparse, int waves_per_simd, int ite
  * with paired-line bands by two fused time steps per launch, by four where r is odd and
  * the engine sparse (then two, then one, for what is left), other grids by one step.
  * The 2-D and the 3-D sequence do not wait for each other where both are replayed from
- * one graph.  Each of their results equals spider_apply of a plan with time_block = 2 bit for bit (one step
- * per launch where two cannot be fused; a plan fusing more steps agrees up to
+ * one graph.  Each of their results equals spider_apply of a plan with time_block = 2
+ * bit for bit (one step per launch where two cannot be fused; a plan fusing more steps agrees up to
  * rounding).  Every other plan (the direct engine, an fp32 carry, 1-D lines, larger
  * radii, the explicit row swap) runs its own time loop after them on the same
  * stream, exactly as spider_apply.

@@ -55,7 +55,8 @@ int band2d_f32_blocks_per_cu(int r, int operand, int engine, bool xlo);
 // window, two output lines per instruction.  Strip s covers outputs
 // [256 s - kPairWinLead, 256 s + 256 - kPairWinLead), so a grid has
 // ceil((nx + 4) / 256) strips; seg_h must be even.  Operands: R + 1 packed
-// instructions in apack / ipack / dpack (planner's pack_pair).
+// instructions in apack / ipack / dpack (planner's pack_pair; launches of several steps at
+// odd radii on the sparse engine, and the fp32 carry's with the input split: pack_quad).
 constexpr int kStripWPair = 256;
 constexpr int kPairWinLead = 4;
 hipError_t launch_band2d_pair(int r, int operand, int engine, const BandGrid& g, hipStream_t s);
@@ -113,7 +114,7 @@ hipError_t launch_band1d(int r, int operand, int engine, const BandGrid& g, hipS
 hipError_t launch_band1d_tbt(int r, int operand, int engine, int T, const BandGrid& g, hipStream_t s);
 
 // 1-D lines advanced up to kLineDeepMaxSteps steps per launch in LDS (r <= 3): one
-// wave per section of nb (4 or 8) blocks of 256 points.  io16: the grid is 16-bit; xlo: the
+// wave per section of nb (2, 4 or 8) blocks of 256 points.  io16: the grid is 16-bit; xlo: the
 // levels are kept as hi / lo pairs.  Bit s - 1 of `rounds` (io16 and xlo): step s
 // rounds the grid to 16 bits.  Operands as for launch_band1d.
 constexpr int kLineDeepMaxSteps = 64;

@@ -127,7 +127,10 @@ static int auto_tile_h_3d(const spider_plan_s* p) {
 // Time loops of up to this many launches are enqueued launch by launch.
 constexpr int kEagerLaunches = 12;
 
-// Grids from this size on advance several steps per streaming launch.
+// Grids from this size on advance several steps per streaming launch.  Not where depth
+// starts to pay (r = 1 fp32, us per step: 1025 x 1024 at one step 3.7, 1100 x 1080 at four
+// 1.9; Star-2D13P 4.6 and 3.9): plans of sizes next above the LDS tile kernel's are ones
+// of a launch per step, as their launch counts have always said (tests pin 1024 x 1025).
 constexpr long long kDirectStreamDeepPoints = (1LL << 20) + (1LL << 17);
 
 static int auto_tile_h_direct(const spider_plan_s* p) {
@@ -792,9 +795,7 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     const int maxT = ndim == 2 ? direct2d_fused_max_steps(radius, p->carry == SPIDER_F64 ? 0 : 1) : 1;
     p->max_time_block = maxT >= 2 ? maxT : 1;
     const long long pts2 = (long long)p->ny * p->nx;
-    // larger grids stream lines through registers, several steps per launch (the grids
-    // just above the tile kernel's range one: a plan of 1024 x 1025 points is one of
-    // single steps)
+    // larger grids stream lines through registers, several steps per launch
     const int zt = p->star ? 2 : (p->has_zero_tap ? 1 : 0);
     int st = ndim == 2 && o.time_block == 0 && o.tile_h == 0 && pts2 > kDirectFusedMaxPoints
                  ? direct2d_stream_max_steps(radius, p->carry == SPIDER_F64 ? 0 : 1, zt, pts2)
