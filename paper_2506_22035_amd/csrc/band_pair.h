@@ -529,14 +529,14 @@ __device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint3
   const int lane = threadIdx.x;
   const int strip = w % g.nstrips, seg = w / g.nstrips;
   const int xp = strip * WIDTH - MARGIN;                // first computed column of every pass (4 mod 8)
-  const int x_lo = T == 1 ? 0 : strip * WIDTH;          // stored columns
+  const int x_lo = strip * WIDTH;                       // stored columns
   // a segment that starts at row 2 mod 4 streams from the pair of rows before it
   const int ys = seg * g.seg_h, y0 = ys & ~3;
   const int hrows = min(g.seg_h, g.ny - ys) + (ys - y0);
   const int npin = (hrows + 1) / 2 + T * R + (T - 1);  // input pairs streamed, in whole bodies of four
   const int nit = (npin + 3) / 4 * 4;
   const int nx = g.nx, ny = g.ny;
-  const int x_hi = T == 1 ? nx : min(nx, x_lo + WIDTH);
+  const int x_hi = min(nx, x_lo + WIDTH);
 
   QuadA<R> A;
   A.load(g, lane);
@@ -559,7 +559,7 @@ __device__ __forceinline__ void band2d_quad_body(const BandGrid& g, int w, uint3
   const PairStore<ALIGNED> ova(xo, line_off, x_lo, x_hi, nx, xp, 2), ovb(xo + 128, line_off, x_lo, x_hi, nx, xp + 128, 2);
   // ragged widths: 16-bit lanes of the intermediate values inside the grid
   uint32_t ma0 = 0, ma1 = 0, mb0 = 0, mb1 = 0;
-  if constexpr (!ALIGNED && T > 1) {
+  if constexpr (!ALIGNED) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const uint32_t half = (e & 1) ? 0xffff0000u : 0x0000ffffu;

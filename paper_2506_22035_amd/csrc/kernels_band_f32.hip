@@ -33,6 +33,8 @@ struct F32Line {
   uint32_t t;
 };
 
+// (whole accesses serve any width: the range check works dword by dword, and an fp32 value
+// is a dword; the fused 1-D kernel still has both forms)
 template <bool ALIGNED>
 __device__ __forceinline__ F32Line load_f32_line(__amdgpu_buffer_rsrc_t rs, uint32_t mvoff, uint32_t tvoff) {
   F32Line L;
@@ -75,7 +77,7 @@ __device__ __forceinline__ F32Line load_h16_line(__amdgpu_buffer_rsrc_t rs, uint
 
 // Output lines are accumulated over kernel rows 0 .. 2R in order (hi product
 // before lo product per row), independent of the segmentation.
-template <int R, int OP, int ENG, bool ALIGNED, bool XLO>
+template <int R, int OP, int ENG, bool XLO>
 __device__ __forceinline__ void band2d_f32_body(const BandGrid& g, int w, uint32_t* lds) {
   constexpr int RR = 2 * R + 1;
   constexpr int U = (RR >= 5) ? RR : 2 * RR;
@@ -123,7 +125,7 @@ __device__ __forceinline__ void band2d_f32_body(const BandGrid& g, int w, uint32
   LineWalk lout(g.out, out_row(-2 * R), y0, y0 + hrows, nx * 4);
   F32Line stg[U];
 #pragma unroll
-  for (int q = 0; q < U; ++q) stg[q] = load_f32_line<ALIGNED>(lin.next(), mvoff, tvoff);
+  for (int q = 0; q < U; ++q) stg[q] = load_f32_line<true>(lin.next(), mvoff, tvoff);
   f32x4 acc[RR];
 #pragma unroll
   for (int s = 0; s < RR; ++s) acc[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -151,11 +153,11 @@ __device__ __forceinline__ void band2d_f32_body(const BandGrid& g, int w, uint32
     if constexpr (DELAY) {
       if (jb > 0) {
 #pragma unroll
-        for (int q = 0; q < U; ++q) store_f32x4<ALIGNED>(lout.next(), ovoff, done[q]);  // output jb - U + q - 2R
+        for (int q = 0; q < U; ++q) store_f32x4<true>(lout.next(), ovoff, done[q]);  // output jb - U + q - 2R
       }
     }
 #pragma unroll
-    for (int q = 0; q < U; ++q) stg[q] = load_f32_line<ALIGNED>(lin.next(), mvoff, tvoff);  // input jb + U + q
+    for (int q = 0; q < U; ++q) stg[q] = load_f32_line<true>(lin.next(), mvoff, tvoff);  // input jb + U + q
     wave_lds_sync();
 #pragma unroll
     for (int q = 0; q < U; ++q) {
@@ -181,25 +183,25 @@ __device__ __forceinline__ void band2d_f32_body(const BandGrid& g, int w, uint32
       if constexpr (DELAY) {
         done[q] = acc[fs];
       } else {
-        store_f32x4<ALIGNED>(lout.next(), ovoff, acc[fs]);  // output jb + q - 2R
+        store_f32x4<true>(lout.next(), ovoff, acc[fs]);  // output jb + q - 2R
       }
       acc[fs] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
   }
   if constexpr (DELAY) {
 #pragma unroll
-    for (int q = 0; q < U; ++q) store_f32x4<ALIGNED>(lout.next(), ovoff, done[q]);  // output nin - U + q - 2R
+    for (int q = 0; q < U; ++q) store_f32x4<true>(lout.next(), ovoff, done[q]);  // output nin - U + q - 2R
   }
 }
 
-template <int R, int OP, int ENG, bool ALIGNED, bool XLO>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((R <= 3 && ENG == 1 && ALIGNED) ? 3 : (R <= 5 ? 2 : 1)))) void band2d_f32_kernel(
+template <int R, int OP, int ENG, bool XLO>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((R <= 3 && ENG == 1) ? 3 : (R <= 5 ? 2 : 1)))) void band2d_f32_kernel(
     BandGrid g) {
   constexpr int RR = 2 * R + 1;
   constexpr int U = (RR >= 5) ? RR : 2 * RR;
   __shared__ uint32_t lds[U * (XLO ? 2 : 1) * kLdsRowDw + 64];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  band2d_f32_body<R, OP, ENG, ALIGNED, XLO>(g, w, lds);
+  band2d_f32_body<R, OP, ENG, XLO>(g, w, lds);
 }
 
 // ----------------------------------------------------------------------------- 1-D
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((R <= 3 && E
 // 16-bit LDS rows in the padded layout; the single kernel row takes one
 // instruction per row part, and the fp32 sums are stored without rounding.  A
 // wave streams seg_h consecutive blocks, staging U blocks ahead.
-template <int R, int OP, int ENG, bool ALIGNED, bool XLO>
+template <int R, int OP, int ENG, bool XLO>
 __device__ __forceinline__ void band1d_f32_body(const BandGrid& g, int w, uint32_t* lds) {
   constexpr int U = 8;
   constexpr int NS = XLO ? 2 : 1;  // LDS rows per block
@@ -235,7 +237,7 @@ __device__ __forceinline__ void band1d_f32_body(const BandGrid& g, int w, uint32
     const bool v = j < nb;
     const uint32_t mvoff = v ? (uint32_t)((x0 - 8 + 4 * lane) * 4) : kOffNone;
     const uint32_t tvoff = (v && lane < 16) ? (uint32_t)((x0 + 248 + lane) * 4) : kOffNone;
-    return load_f32_line<ALIGNED>(rin, mvoff, tvoff);
+    return load_f32_line<true>(rin, mvoff, tvoff);
   };
   auto out_off = [&](int j) {
     const int x = 256 * (b0 + j) - 8 + 16 * (lane & 15) + 4 * (lane >> 4);
@@ -266,7 +268,7 @@ __device__ __forceinline__ void band1d_f32_body(const BandGrid& g, int w, uint32
     }
     if (jb > 0) {
 #pragma unroll
-      for (int q = 0; q < U; ++q) store_f32x4<ALIGNED>(rout, out_off(jb - U + q), done[q]);
+      for (int q = 0; q < U; ++q) store_f32x4<true>(rout, out_off(jb - U + q), done[q]);
     }
 #pragma unroll
     for (int q = 0; q < U; ++q) stg[q] = load_blk(jb + U + q);
@@ -285,14 +287,14 @@ __device__ __forceinline__ void band1d_f32_body(const BandGrid& g, int w, uint32
     }
   }
 #pragma unroll
-  for (int q = 0; q < U; ++q) store_f32x4<ALIGNED>(rout, out_off(nbody * U - U + q), done[q]);
+  for (int q = 0; q < U; ++q) store_f32x4<true>(rout, out_off(nbody * U - U + q), done[q]);
 }
 
-template <int R, int OP, int ENG, bool ALIGNED, bool XLO>
+template <int R, int OP, int ENG, bool XLO>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XLO ? 2 : 3))) void band1d_f32_kernel(BandGrid g) {
   __shared__ uint32_t lds[8 * (XLO ? 2 : 1) * kLdsRowDw + 64];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  band1d_f32_body<R, OP, ENG, ALIGNED, XLO>(g, w, lds);
+  band1d_f32_body<R, OP, ENG, XLO>(g, w, lds);
 }
 
 // T = 2..4 fp32-carry time steps per launch on the 1-D band engine.  The block
@@ -479,7 +481,7 @@ constexpr bool row_used3(int a) {
   return (MASK >> a) & 1u;
 }
 
-template <int R, int OP, int ENG, bool ALIGNED, bool XLO, uint32_t MASK>
+template <int R, int OP, int ENG, bool XLO, uint32_t MASK>
 __device__ __forceinline__ void band3d_f32_body(const BandGrid& g, int w, uint32_t* lds) {
   constexpr int RR = 2 * R + 1;
   constexpr int NR = RR * RR;
@@ -541,7 +543,7 @@ __device__ __forceinline__ void band3d_f32_body(const BandGrid& g, int w, uint32
       const bool valid = zv && (uint32_t)(yb0 - R + l) < (uint32_t)ny;
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
           reinterpret_cast<void*>(in_addr + (uint64_t)(l * lb)), (short)0, valid ? lb : 0, kRsrcWord3);
-      stg[l] = load_f32_line<ALIGNED>(rs, mvoff, tvoff);
+      stg[l] = load_f32_line<true>(rs, mvoff, tvoff);
     }
     in_addr += (uint64_t)pbytes;
     ++zrel;
@@ -553,7 +555,7 @@ __device__ __forceinline__ void band3d_f32_body(const BandGrid& g, int w, uint32
       const bool ov = k < hz && yb0 + b < ny;
       const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
           reinterpret_cast<void*>(out_addr + (uint64_t)(b * lb)), (short)0, ov ? lb : 0, kRsrcWord3);
-      store_f32x4<ALIGNED>(rs, ovoff, vals[b]);
+      store_f32x4<true>(rs, ovoff, vals[b]);
     }
     out_addr += (uint64_t)pbytes;
   };
@@ -644,108 +646,102 @@ constexpr uint32_t star_mask3_f32() {
   return m;
 }
 
-template <int R, int OP, int ENG, bool ALIGNED, bool XLO, uint32_t MASK>
+template <int R, int OP, int ENG, bool XLO, uint32_t MASK>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void band3d_f32_kernel(BandGrid g) {
   constexpr int NLY = kRowsY3 + 2 * R;
   __shared__ uint32_t lds[NLY * (XLO ? 2 : 1) * kLdsRowDw + 64];
   const int w = xcd_remap(blockIdx.x, gridDim.x);
-  band3d_f32_body<R, OP, ENG, ALIGNED, XLO, MASK>(g, w, lds);
+  band3d_f32_body<R, OP, ENG, XLO, MASK>(g, w, lds);
 }
 
 namespace {
 
-template <int OP, int ENG, bool AL, bool XLO>
-hipError_t dispatch_f32(int r, const BandGrid& g, hipStream_t s) {
+template <int OP, int ENG, bool XLO>
+hipError_t dispatch_f32_split(int r, const BandGrid& g, hipStream_t s) {
   const dim3 grid(g.nblocks), block(64);
   switch (r) {
-    case 1: hipLaunchKernelGGL((band2d_f32_kernel<1, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 2: hipLaunchKernelGGL((band2d_f32_kernel<2, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 3: hipLaunchKernelGGL((band2d_f32_kernel<3, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 4: hipLaunchKernelGGL((band2d_f32_kernel<4, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 5: hipLaunchKernelGGL((band2d_f32_kernel<5, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 6: hipLaunchKernelGGL((band2d_f32_kernel<6, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 7: hipLaunchKernelGGL((band2d_f32_kernel<7, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
+    case 1: hipLaunchKernelGGL((band2d_f32_kernel<1, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 2: hipLaunchKernelGGL((band2d_f32_kernel<2, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 3: hipLaunchKernelGGL((band2d_f32_kernel<3, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 4: hipLaunchKernelGGL((band2d_f32_kernel<4, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 5: hipLaunchKernelGGL((band2d_f32_kernel<5, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 6: hipLaunchKernelGGL((band2d_f32_kernel<6, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 7: hipLaunchKernelGGL((band2d_f32_kernel<7, OP, ENG, XLO>), grid, block, 0, s, g); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <int OP, int ENG>
-hipError_t dispatch_f32_al(int r, bool xlo, const BandGrid& g, hipStream_t s) {
-  // 16-byte accesses for any width: the range check works dword by dword, and an
-  // fp32 value is a dword
-  return xlo ? dispatch_f32<OP, ENG, true, true>(r, g, s) : dispatch_f32<OP, ENG, true, false>(r, g, s);
+hipError_t dispatch_f32(int r, bool xlo, const BandGrid& g, hipStream_t s) {
+  return xlo ? dispatch_f32_split<OP, ENG, true>(r, g, s) : dispatch_f32_split<OP, ENG, false>(r, g, s);
 }
 
 }  // namespace
 
 hipError_t launch_band2d_f32(int r, int operand, int engine, bool xlo, const BandGrid& g, hipStream_t s) {
-  if (operand == 2 && engine == 1) return dispatch_f32_al<2, 1>(r, xlo, g, s);
-  if (operand == 2 && engine == 2) return dispatch_f32_al<2, 2>(r, xlo, g, s);
-  if (operand == 3 && engine == 1) return dispatch_f32_al<3, 1>(r, xlo, g, s);
-  if (operand == 3 && engine == 2) return dispatch_f32_al<3, 2>(r, xlo, g, s);
+  if (operand == 2 && engine == 1) return dispatch_f32<2, 1>(r, xlo, g, s);
+  if (operand == 2 && engine == 2) return dispatch_f32<2, 2>(r, xlo, g, s);
+  if (operand == 3 && engine == 1) return dispatch_f32<3, 1>(r, xlo, g, s);
+  if (operand == 3 && engine == 2) return dispatch_f32<3, 2>(r, xlo, g, s);
   return hipErrorInvalidValue;
 }
 
 namespace {
-template <int OP, int ENG, bool AL, bool XLO>
-hipError_t dispatch3d_f32(const BandGrid& g, hipStream_t s) {
+template <int OP, int ENG, bool XLO>
+hipError_t dispatch3d_f32_split(const BandGrid& g, hipStream_t s) {
   const dim3 grid(g.nblocks), block(64);
   if ((g.rowmask & ~star_mask3_f32<1>()) == 0)  // every non-zero row lies on the star
-    hipLaunchKernelGGL((band3d_f32_kernel<1, OP, ENG, AL, XLO, star_mask3_f32<1>()>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((band3d_f32_kernel<1, OP, ENG, XLO, star_mask3_f32<1>()>), grid, block, 0, s, g);
   else
-    hipLaunchKernelGGL((band3d_f32_kernel<1, OP, ENG, AL, XLO, box_mask3_f32<1>()>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((band3d_f32_kernel<1, OP, ENG, XLO, box_mask3_f32<1>()>), grid, block, 0, s, g);
   return hipGetLastError();
 }
 template <int OP, int ENG>
-hipError_t dispatch3d_f32_al(bool xlo, const BandGrid& g, hipStream_t s) {
-  // 16-byte accesses for any width: the range check works dword by dword, and an
-  // fp32 value is a dword
-  return xlo ? dispatch3d_f32<OP, ENG, true, true>(g, s) : dispatch3d_f32<OP, ENG, true, false>(g, s);
+hipError_t dispatch3d_f32(bool xlo, const BandGrid& g, hipStream_t s) {
+  return xlo ? dispatch3d_f32_split<OP, ENG, true>(g, s) : dispatch3d_f32_split<OP, ENG, false>(g, s);
 }
 template <int OP, int ENG, bool XLO>
 int occ3d_f32(uint32_t rowmask) {
   int nb = 0;
   hipError_t e;
   if ((rowmask & ~star_mask3_f32<1>()) == 0)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, band3d_f32_kernel<1, OP, ENG, true, XLO, star_mask3_f32<1>()>,
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, band3d_f32_kernel<1, OP, ENG, XLO, star_mask3_f32<1>()>,
                                                      64, 0);
   else
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, band3d_f32_kernel<1, OP, ENG, true, XLO, box_mask3_f32<1>()>,
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, band3d_f32_kernel<1, OP, ENG, XLO, box_mask3_f32<1>()>,
                                                      64, 0);
   return e == hipSuccess ? nb : 0;
 }
 }  // namespace
 
 namespace {
-template <int OP, int ENG, bool AL, bool XLO>
-hipError_t dispatch1d_f32(int r, const BandGrid& g, hipStream_t s) {
+template <int OP, int ENG, bool XLO>
+hipError_t dispatch1d_f32_split(int r, const BandGrid& g, hipStream_t s) {
   const dim3 grid(g.nblocks), block(64);
   switch (r) {
-    case 1: hipLaunchKernelGGL((band1d_f32_kernel<1, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 2: hipLaunchKernelGGL((band1d_f32_kernel<2, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 3: hipLaunchKernelGGL((band1d_f32_kernel<3, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 4: hipLaunchKernelGGL((band1d_f32_kernel<4, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 5: hipLaunchKernelGGL((band1d_f32_kernel<5, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 6: hipLaunchKernelGGL((band1d_f32_kernel<6, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
-    case 7: hipLaunchKernelGGL((band1d_f32_kernel<7, OP, ENG, AL, XLO>), grid, block, 0, s, g); break;
+    case 1: hipLaunchKernelGGL((band1d_f32_kernel<1, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 2: hipLaunchKernelGGL((band1d_f32_kernel<2, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 3: hipLaunchKernelGGL((band1d_f32_kernel<3, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 4: hipLaunchKernelGGL((band1d_f32_kernel<4, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 5: hipLaunchKernelGGL((band1d_f32_kernel<5, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 6: hipLaunchKernelGGL((band1d_f32_kernel<6, OP, ENG, XLO>), grid, block, 0, s, g); break;
+    case 7: hipLaunchKernelGGL((band1d_f32_kernel<7, OP, ENG, XLO>), grid, block, 0, s, g); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 template <int OP, int ENG>
-hipError_t dispatch1d_f32_al(int r, bool xlo, const BandGrid& g, hipStream_t s) {
-  // 16-byte accesses for any width: the range check works dword by dword, and an
-  // fp32 value is a dword
-  return xlo ? dispatch1d_f32<OP, ENG, true, true>(r, g, s) : dispatch1d_f32<OP, ENG, true, false>(r, g, s);
+hipError_t dispatch1d_f32(int r, bool xlo, const BandGrid& g, hipStream_t s) {
+  return xlo ? dispatch1d_f32_split<OP, ENG, true>(r, g, s) : dispatch1d_f32_split<OP, ENG, false>(r, g, s);
 }
 }  // namespace
 
 hipError_t launch_band1d_f32(int r, int operand, int engine, bool xlo, const BandGrid& g, hipStream_t s) {
-  if (operand == 2 && engine == 1) return dispatch1d_f32_al<2, 1>(r, xlo, g, s);
-  if (operand == 2 && engine == 2) return dispatch1d_f32_al<2, 2>(r, xlo, g, s);
-  if (operand == 3 && engine == 1) return dispatch1d_f32_al<3, 1>(r, xlo, g, s);
-  if (operand == 3 && engine == 2) return dispatch1d_f32_al<3, 2>(r, xlo, g, s);
+  if (operand == 2 && engine == 1) return dispatch1d_f32<2, 1>(r, xlo, g, s);
+  if (operand == 2 && engine == 2) return dispatch1d_f32<2, 2>(r, xlo, g, s);
+  if (operand == 3 && engine == 1) return dispatch1d_f32<3, 1>(r, xlo, g, s);
+  if (operand == 3 && engine == 2) return dispatch1d_f32<3, 2>(r, xlo, g, s);
   return hipErrorInvalidValue;
 }
 
@@ -831,10 +827,10 @@ hipError_t launch_band1d_f32_tbt(int r, int operand, int engine, bool xlo, int T
 
 hipError_t launch_band3d_f32(int r, int operand, int engine, bool xlo, const BandGrid& g, hipStream_t s) {
   if (r != 1) return hipErrorInvalidValue;
-  if (operand == 2 && engine == 1) return dispatch3d_f32_al<2, 1>(xlo, g, s);
-  if (operand == 2 && engine == 2) return dispatch3d_f32_al<2, 2>(xlo, g, s);
-  if (operand == 3 && engine == 1) return dispatch3d_f32_al<3, 1>(xlo, g, s);
-  if (operand == 3 && engine == 2) return dispatch3d_f32_al<3, 2>(xlo, g, s);
+  if (operand == 2 && engine == 1) return dispatch3d_f32<2, 1>(xlo, g, s);
+  if (operand == 2 && engine == 2) return dispatch3d_f32<2, 2>(xlo, g, s);
+  if (operand == 3 && engine == 1) return dispatch3d_f32<3, 1>(xlo, g, s);
+  if (operand == 3 && engine == 2) return dispatch3d_f32<3, 2>(xlo, g, s);
   return hipErrorInvalidValue;
 }
 
@@ -852,7 +848,7 @@ int band2d_f32_blocks_per_cu(int r, int operand, int engine, bool xlo) {
   hipError_t e = hipErrorInvalidValue;
 #define SPIDER_OCC_F32(RV, OPV, ENGV, XV)                                                                \
   if (r == RV && operand == OPV && engine == ENGV && xlo == XV)                                          \
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, band2d_f32_kernel<RV, OPV, ENGV, true, XV>, 64, 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, band2d_f32_kernel<RV, OPV, ENGV, XV>, 64, 0);
 #define SPIDER_OCC_F32_R(RV) \
   SPIDER_OCC_F32(RV, 2, 1, true) SPIDER_OCC_F32(RV, 2, 1, false) SPIDER_OCC_F32(RV, 2, 2, true) \
   SPIDER_OCC_F32(RV, 2, 2, false) SPIDER_OCC_F32(RV, 3, 1, true) SPIDER_OCC_F32(RV, 3, 1, false) \

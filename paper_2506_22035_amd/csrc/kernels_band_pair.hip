@@ -53,19 +53,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(ENG == 1 ? 3
   const int w = xcd_remap(blockIdx.x, gridDim.x);
   if constexpr (use_quad<R, ENG, 2>()) {
     quad_bodies<R, OP, ALIGNED, 2>(g, w, lds);
-    return;
-  }
-  if constexpr (ENG == 1) {  // (a second body would spill the dense variants)
-    // interior waves: columns [xp, xp + 256) and rows [y0 - 2R, y0 + hrows + 2R + 2) inside the grid
-    const int strip = w % g.nstrips, seg = w / g.nstrips;
-    const int xp = strip * kStripWPair2 - kPairWinLead;
-    const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
-    if (xp >= 0 && xp + (ALIGNED ? 256 : 260) <= g.nx && y0 - 2 * R >= 0 && y0 + hrows + 2 * R + 2 <= g.ny) {
-      if constexpr (!use_quad<R, ENG, 2>()) band2d_pair_tb2_body<R, OP, ENG, true, false>(g, w, lds);
-      return;
+  } else {
+    if constexpr (ENG == 1) {  // (a second body would spill the dense variants)
+      // interior waves: columns [xp, xp + 256) and rows [y0 - 2R, y0 + hrows + 2R + 2) inside the grid
+      const int strip = w % g.nstrips, seg = w / g.nstrips;
+      const int xp = strip * kStripWPair2 - kPairWinLead;
+      const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
+      if (xp >= 0 && xp + (ALIGNED ? 256 : 260) <= g.nx && y0 - 2 * R >= 0 && y0 + hrows + 2 * R + 2 <= g.ny) {
+        band2d_pair_tb2_body<R, OP, ENG, true, false>(g, w, lds);
+        return;
+      }
     }
+    band2d_pair_tb2_body<R, OP, ENG, ALIGNED, true>(g, w, lds);
   }
-  if constexpr (!use_quad<R, ENG, 2>()) band2d_pair_tb2_body<R, OP, ENG, ALIGNED, true>(g, w, lds);
 }
 
 // ----------------------------------------------------------------------------- T fused steps
@@ -265,23 +265,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void ba
   const int w = xcd_remap(blockIdx.x, gridDim.x);
   if constexpr (use_quad<R, ENG, T>()) {
     quad_bodies<R, OP, ALIGNED, T>(g, w, lds);
-    return;
-  }
-  // interior waves (most of a large grid) skip the masking of intermediate values:
-  // columns [xp, xp + 256) and rows [y0 - T R, y0 + hrows + T R + 2) inside the grid
-  const int strip = w % g.nstrips, seg = w / g.nstrips;
-  const int xp = strip * pair_tb_width(T, R) - pair_tb_margin(T, R);
-  const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
-  const bool interior = xp >= 0 && xp + (ALIGNED ? 256 : 260) <= g.nx && y0 - T * R >= 0 && y0 + hrows + T * R + 2 <= g.ny;
-  (void)interior;
-  if constexpr (ENG == 1) {
-    if (interior) {
-      if constexpr (!use_quad<R, ENG, T>()) band2d_pair_tbt_body<R, OP, ENG, true, T, false>(g, w, lds);
-      return;
+  } else {
+    if constexpr (ENG == 1) {  // (the dense engine keeps one body: its second copy would spill)
+      // interior waves (most of a large grid) skip the masking of intermediate values:
+      // columns [xp, xp + 256) and rows [y0 - T R, y0 + hrows + T R + 2) inside the grid
+      const int strip = w % g.nstrips, seg = w / g.nstrips;
+      const int xp = strip * pair_tb_width(T, R) - pair_tb_margin(T, R);
+      const int y0 = seg * g.seg_h, hrows = min(g.seg_h, g.ny - y0);
+      if (xp >= 0 && xp + (ALIGNED ? 256 : 260) <= g.nx && y0 - T * R >= 0 && y0 + hrows + T * R + 2 <= g.ny) {
+        band2d_pair_tbt_body<R, OP, ENG, true, T, false>(g, w, lds);
+        return;
+      }
     }
+    band2d_pair_tbt_body<R, OP, ENG, ALIGNED, T, true>(g, w, lds);
   }
-  // (the dense engine keeps one body: its second copy would spill)
-  if constexpr (!use_quad<R, ENG, T>()) band2d_pair_tbt_body<R, OP, ENG, ALIGNED, T, true>(g, w, lds);
 }
 
 namespace {
