@@ -54,6 +54,17 @@ size_t dtype_bytes(int dt) {
 
 static int model_rows_2d(const spider_plan_s* p, int T, long long nstrips, int max_waves);
 
+// Whether a 2-D plan's launch of T steps takes its height from the launch model or from one
+// resident round of waves.  The model is of chains; the largest grids of the dense engine
+// and of single steps with 16-point bands wait for the matrix pipe or for memory instead,
+// and a round has the fewest halo lines (us per step, model and round: dense, fp16, r = 5
+// 10240^2 115 and 112, 8192^2 76.0 and 74.3, 6000^2 44.3 and 45.9, 3000 x 4000 20.4 and
+// 24.1; fp32 carry, split 3, r = 5 8192^2 125 and 123, 5000^2 51.9 and 55.1).
+static bool use_row_model(const spider_plan_s* p, int T) {
+  return p->auto_rows && ((p->engine == SPIDER_ENGINE_SPARSE && (p->band_h == 8 || T > 1)) ||
+                          (long long)p->ny * p->nx < (1LL << 26));
+}
+
 // Segment height of the 2-D band kernel: enough rows per wave that one launch
 // fills every CU once (all waves resident, no tail round), but not fewer than
 // 16 rows so the 2r halo rows stay a small fraction of the streamed rows.
@@ -68,7 +79,7 @@ static int auto_tile_h_2d(const spider_plan_s* p) {
   const long long slots = (long long)ncu * per_cu;
   const long long nstrips = p->band_h == 8 ? (p->nx + kPairWinLead + kStripWPair - 1) / kStripWPair
                                            : (p->nx + 8 + kStripW - 1) / kStripW;
-  if (p->auto_rows) return model_rows_2d(p, 1, nstrips, per_cu / 4);
+  if (use_row_model(p, 1)) return model_rows_2d(p, 1, nstrips, per_cu / 4);
   // segments per strip that keep every wave resident: ceil(ny / h) * nstrips <= slots
   const long long segs = std::max<long long>(1, slots / nstrips);
   long long h = (p->ny + segs - 1) / segs;
@@ -370,7 +381,7 @@ static int auto_tile_h_tb2(const spider_plan_s* p) {
                : p->time_block > 2 ? band2d_pair_tbt_blocks_per_cu(p->r, p->operand, p->engine, p->time_block)
                                    : band2d_pair_tb2_blocks_per_cu(p->r, p->operand, p->engine);
   if (per_cu <= 0) per_cu = 8;
-  if (p->auto_rows) return model_rows_2d(p, p->time_block, p->grid_tb2.nstrips, per_cu / 4);
+  if (use_row_model(p, p->time_block)) return model_rows_2d(p, p->time_block, p->grid_tb2.nstrips, per_cu / 4);
   // a third wave per SIMD adds less than the taller segments of two save in halo
   // rows (two fused steps, paired bands: Box-2D49P 10240^2 1792 GStencil/s at three
   // waves per SIMD, 2067 at two; Star-2D13P 8192^2 1780 against 2064)
