@@ -36,11 +36,9 @@ struct spider_plan_s {
   uint32_t rowmask = 0;   // rows with a non-zero tap
   bool has_zero_tap = false;
   bool star = false;  // direct engine: every non-zero tap on an axis through the centre
-  void* d_apack = nullptr;
-  void* d_ipack = nullptr;
-  void* d_dpack = nullptr;
+  void* d_packed = nullptr;  // matrix operands: apack, ipack and dpack
   // paired bands, odd radii, sparse engine: operands of the launches that run quads (where
-  // single-step launches do not, behind theirs in d_apack and d_ipack), else null
+  // single-step launches do not, behind theirs in apack and ipack), else null
   const uint4* quad_apack = nullptr;
   const uint32_t* quad_ipack = nullptr;
   void* d_coeffs = nullptr;

