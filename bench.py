@@ -142,26 +142,28 @@ def roofline(torch, sp, plan, xd, elem, npts, grid, operand, stream, headline_tr
     sustained = {"value": round(gstencil(npts, steps * n_s, ms_s), 2), "seconds": round(ms_s * 1e-3, 3),
                  "passes": n_s, "ms_per_step": round(ms_s / n_s, 4),
                  "method": "passes of the workload from the same input, back to back"}
-    nl = max(1, steps // tb)              # fused launches per roofline pass
-    n_r = max(20, int(math.ceil(0.5 * SUSTAIN_S * 1e3 / max(pass_ms * nl * tb / steps, 1e-3))))
-    plan.apply(xd, yl, nl * tb, stream=stream)
+    steps_r = max(1, steps // tb) * tb    # steps and launches of a roofline pass
+    nl = plan.work(steps_r)[0]            # (a 1-D line's launches advance several time_blocks)
+    n_r = max(20, int(math.ceil(0.5 * SUSTAIN_S * 1e3 / max(pass_ms * steps_r / steps, 1e-3))))
+    plan.apply(xd, yl, steps_r, stream=stream)
     torch.cuda.synchronize()
     e0.record(stream)
     for _ in range(n_r):
-        plan.apply(xd, yl, nl * tb, stream=stream)
+        plan.apply(xd, yl, steps_r, stream=stream)
     e1.record(stream)
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1)
     del yl
     avg_s = ms * 1e-3 / (n_r * nl)
     compulsory = npts * 2 * elem          # one read and one write of the state per launch
-    charged = compulsory * tb             # the same per time step, all steps of the launch
+    charged = compulsory * steps_r // nl  # the same per time step, all steps of the launch
     traffic = headline_traffic(tb, info["tile_h2"], grid)
     hbm_bytes = traffic if traffic is not None else compulsory
     hbm_frac = hbm_bytes / avg_s / 1e9 / HBM_PEAK_GBS
-    _, n_mi = plan.work(tb)
+    n_mi = plan.work(steps_r)[1]
     roof = {}
     if n_mi is not None and n_mi > 0:
+        n_mi = n_mi // nl
         flop = n_mi * MACS_PER_INSTRUCTION * 2
         mfma_tflops = flop / avg_s / 1e12
         mfma_frac = mfma_tflops / MFMA_PEAK_TFLOPS
@@ -183,7 +185,8 @@ def roofline(torch, sp, plan, xd, elem, npts, grid, operand, stream, headline_tr
         roof["mfma"] = {"instructions_per_launch": n_mi, "operand": operand,
                         "macs_per_instruction": MACS_PER_INSTRUCTION, "TFLOPs": round(mfma_tflops, 1),
                         "frac": round(mfma_frac, 4)}
-    roof.update({"avg_launch_us": round(avg_s * 1e6, 2), "time_steps_per_launch": tb,
+    roof.update({"avg_launch_us": round(avg_s * 1e6, 2),
+                 "time_steps_per_launch": steps_r // nl if steps_r % nl == 0 else round(steps_r / nl, 2),
                  "launch_timing": "%d passes of %d fused launches from the workload's input (%.0f ms), after the "
                                   "timed passes" % (n_r, nl, ms),
                  "alg_GBs_charged": round(charged / avg_s / 1e9, 1),
@@ -209,10 +212,16 @@ def matrix_ceiling(sp, engine, stream, waves=(2, 4), iterations=200000):
     return out
 
 
-def kernel_name(info, shape, carry, engine, r, row_swap):
+def kernel_name(plan, info, shape, carry, engine, r, row_swap, automatic):
+    """The plan's dominant kernel; automatic: neither a depth nor a height was asked for."""
     tb = info["time_block"]
     if engine == "direct":
-        kname = "direct2d_fused_kernel" if (len(shape) == 2 and tb > 1) else "direct%dd_kernel" % len(shape)
+        if len(shape) == 2 and r <= 3 and automatic and shape[0] * shape[1] > 1 << 20:
+            kname = "direct2d_stream_kernel"
+        else:
+            kname = "direct2d_fused_kernel" if (len(shape) == 2 and tb > 1) else "direct%dd_kernel" % len(shape)
+    elif len(shape) == 1 and plan.work(8 * tb)[0] < 8:
+        kname = "line_deep_kernel"
     elif carry == "f32":
         kname = ("band2d_pair_f32_kernel" if info["band_height"] == 8 else "band2d_f32_kernel")
     elif len(shape) == 1:
@@ -221,9 +230,11 @@ def kernel_name(info, shape, carry, engine, r, row_swap):
         kname = "band3d_kernel"
     elif info["band_height"] == 8:
         kname = {1: "band2d_pair_kernel", 2: "band2d_pair_tb2_kernel"}.get(tb, "band2d_pair_tbt_kernel")
+    elif r > 3 and tb == 2:
+        kname = "band2d_wide2_kernel"
     else:
         kname = "band2d_tb2_kernel" if tb == 2 else "band2d_kernel"
-    return kname + "<r=%d,%s,%s%s%s>" % (r, carry, engine, ",T=%d" % tb if tb > 1 else "",
+    return kname + "<r=%d,%s,%s%s%s>" % (r, carry, engine, ",T=%d" % tb if tb > 1 and kname != "line_deep_kernel" else "",
                                          ",explicit row swap" if row_swap == "explicit" else "")
 
 
@@ -552,7 +563,7 @@ def other_configs(torch, sp, si, stream, oracle):
         ef = full_grid_error(oracle, wl["coeffs"], xf, wl["steps"], gf, "f32s3")
         del gf, xf
         # 16-bit grid, split 3: the levels inside a fused launch kept as hi/lo pairs,
-        # the grid rounded to fp16 once per launch instead of once per step
+        # the grid rounded to fp16 every time_block steps instead of every step
         vh, ih, gh, xh = workload_run(torch, sp, si, name, "f16", "sparse", 3, 5, stream)
         eh = full_grid_error(oracle, wl["coeffs"], xh, wl["steps"], gh, "f16")
         del gh, xh
@@ -682,7 +693,8 @@ def main():
 
     roof, sustained = roofline(torch, sp, plan, xd, elem, npts, shape, operand, stream, traffic_lookup, T,
                                ms_per_step)
-    roof["kernel"] = kernel_name(info, shape, args.carry, args.engine, rr, args.row_swap)
+    roof["kernel"] = kernel_name(plan, info, shape, args.carry, args.engine, rr, args.row_swap,
+                                 not args.time_block and not args.tile_h)
     ceiling = None
     if "mfma" in roof and not args.no_extras:
         # the matrix pipe's attainable rate at the fused kernel's residency (two waves per
