@@ -8,7 +8,7 @@
 // one LDS line, rounded to the carry as a stored grid would be and zero outside the grid,
 // and memory is passed once for both.  Fp16, 10240^2, us per step, one step and two: r = 4
 // 102 and 63, r = 5 105 and 71, r = 6 109 and 82, r = 7 114 and 93, where the matrix
-// instructions of two waves per SIMD are the time left.
+// instructions are the largest bound (the pipe is busy 68 % of a launch by its counter).
 //
 // Registers decide the shape: 15 operand rows and 2 x 15 accumulators are 188 of the 256
 // that two waves per SIMD leave, so input lines are staged a third of a turn at a time

@@ -16,7 +16,8 @@
 // 2048 x 2051 26.7 / 6.7; 9 points fp32 8192^2 121 / 25 (eight levels), 4096^2
 // 26.7 / 8.6 (four); fp64 6000^2 133 / 38 (r = 1, four levels), 136 / 70 (star r = 3,
 // two).  At four levels of Star-2D13P the vector ALUs are the bound (52 multiply-adds
-// and 6 shifts per lane, line and level), at r = 1 still the memory.
+// and 6 shifts per lane, line and level; 70 % of a launch's cycles by their counter), at
+// r = 1 still the memory.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
